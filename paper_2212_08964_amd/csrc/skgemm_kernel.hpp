@@ -20,13 +20,19 @@
 //
 // LDS layouts (no padding; 16-byte chunks XOR-swizzled per row so that the
 // fragment reads of one instruction fall on distinct banks):
-//  * K-contiguous operand: [rows][128 bytes of k]; chunk c of row r sits at
-//    position c ^ (r mod 8) ^ ((r / 8) mod 2), so the 16-byte reads of 16
-//    consecutive rows (one LDS cycle of 64 banks) touch distinct banks.
+//  * K-contiguous operand: [rows][128 bytes of k].  A 16-byte read of a wave is
+//    served in four cycles of 64 banks, each for the lanes l with l mod 32 in
+//    {0-3, 12-15, 20-27} or {4-11, 16-19, 28-31} of one half of the wave.
+//    Where a half reads 32 rows at one chunk, chunk c of row r sits at
+//    position c ^ (r mod 8) ^ ((r / 8) mod 2); for 16-bit types, where it reads
+//    16 rows at two neighbouring chunks, at c ^ (r mod 8).  Both keep the
+//    lanes of a cycle on distinct banks (the other type's position would give
+//    two-way conflicts).
 //  * MN-contiguous operand: [k][512 bytes of rows]; chunk c of row k sits at
-//    position c ^ 4 (k mod 4) for 16-bit types (read with the LDS transpose
-//    read, four k of one column per lane) and c ^ 8 ((k / 4) mod 2) for FP32
-//    (read with plain 4-byte reads).
+//    position c ^ 4 (k mod 4) ^ 2 ((k / 8) mod 2) for 16-bit types (read with
+//    the LDS transpose read, four k of one column per lane; two groups of 16
+//    lanes eight k apart are served together) and c ^ 8 ((k / 4) mod 2) for
+//    FP32 (read with plain 4-byte reads).
 
 #pragma once
 
@@ -107,8 +113,12 @@ template <class C> struct PrioOf<C, std::void_t<decltype(C::PRIO)>> { static con
 template <class C, class = void> struct ConvOf { static constexpr bool value = false; };
 template <class C> struct ConvOf<C, std::void_t<decltype(C::CONV)>> { static constexpr bool value = C::CONV; };
 
+// Waves that split a slab's k between them.
+template <class C, class = void> struct WkOf { static constexpr int value = 1; };
+template <class C> struct WkOf<C, std::void_t<decltype(C::WK)>> { static constexpr int value = C::WK; };
+
 template <int DT, int V>
-constexpr int kThreadsOf = 64 * Cfg<DT, V>::WM * Cfg<DT, V>::WN;
+constexpr int kThreadsOf = 64 * Cfg<DT, V>::WM * Cfg<DT, V>::WN * WkOf<Cfg<DT, V>>::value;
 
 // Waves per SIMD the register budget must allow: two workgroups per CU for
 // the 4-wave tiles (the 8-wave tiles get two waves per SIMD from one, and the
@@ -143,6 +153,15 @@ __device__ __forceinline__ void dma16(const i32x4& desc, uint32_t voff, uint32_t
                  :
                  : "v"(voff), "s"(desc), "s"(lds)
                  : "memory");
+}
+
+// The same at LDS address lds + OFF.
+template <int OFF>
+__device__ __forceinline__ void dma16_at(const i32x4& desc, uint32_t voff, uint32_t lds) {
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+                 :
+                 : "v"(voff), "s"(desc), "s"(lds), "n"(OFF)
+                 : "memory", "scc");
 }
 
 // Workgroup barrier between pipeline steps, without the memory fence of
@@ -180,9 +199,12 @@ __device__ __forceinline__ int opaque(int x) {
 // Position swizzle of a row of a slab in LDS (see the layout note above).
 template <int EB, bool KC, int ROWB>
 __device__ __forceinline__ int swz(int row) {
-    if constexpr (KC && ROWB == 128) return (row & 7) ^ ((row >> 3) & 1);
+    if constexpr (KC && ROWB >= 256) return row & 15;
+    else if constexpr (KC && ROWB == 128 && EB == 2) return row & 7;
+    else if constexpr (KC && ROWB == 128) return (row & 7) ^ ((row >> 3) & 1);
     else if constexpr (KC) return (row >> 2) & 3;          // 64-byte rows: 4 chunks
     else if constexpr (EB == 4) return 8 * ((row >> 2) & 1);
+    else if constexpr (EB == 2) return (4 * (row & 3)) ^ (2 * ((row >> 3) & 1));
     else return 4 * (row & 3);
 }
 
@@ -205,7 +227,8 @@ struct Slab {
     static constexpr int NW = THREADS / 64;
     static constexpr int BLOCKS = BYTES / 1024;
     static constexpr int PER_WAVE = BLOCKS / NW;
-    static_assert(!KC || BK * EB == 128 || BK * EB == 64, "K-contiguous slab rows must be 64 or 128 bytes");
+    static_assert(!KC || BK * EB == 64 || BK * EB == 128 || ((BK * EB == 256 || BK * EB == 512) && EB == 2),
+                  "K-contiguous slab rows must be 64 or 128 bytes (256 or 512 for 16-bit types)");
     static_assert(KC || ROWB == 1024 || ROWB == 512 || ROWB == 256,
                   "MN-contiguous slab rows must be 256, 512 or 1024 bytes");
     static_assert(BLOCKS % NW == 0, "slab must split evenly over the waves");
@@ -214,6 +237,9 @@ struct Slab {
     const unsigned char* base;   // operand address of (outer o0, k of the first iteration)
     int64_t bytes;               // operand bytes from base to its end
     int64_t step;                // bytes between consecutive k-iterations
+    uint32_t ldb;                // leading dimension, bytes
+    uint64_t ahead;              // address of the next slab to prepare (they are prepared in order) ...
+    int64_t left;                // ... and the operand's bytes from there on
 
     __device__ __forceinline__ void init(const void* X, int64_t ld, int o0, int dout, int kbeg, int K,
                                          int tid) {
@@ -228,11 +254,15 @@ struct Slab {
             bytes = ((int64_t)(K - k0 - 1) * ld + (dout - o0)) * EB;
             step = (int64_t)BK * ld * EB;
         }
+        ldb = uint32_t(ld * EB);
+        ahead = reinterpret_cast<uint64_t>(base);
+        left = bytes;
 #pragma unroll
-        for (int j = 0; j < PER_WAVE; ++j) {
-            const int row = chunk_row(j, tid);
-            voff[j] = uint32_t(row) * uint32_t(ld * EB) + uint32_t(chunk_col(j, tid) * 16);
-        }
+        for (int j = 0; j < PER_WAVE; ++j) voff[j] = chunk_off(j, tid);
+    }
+
+    __device__ __forceinline__ uint32_t chunk_off(int j, int tid) const {
+        return uint32_t(chunk_row(j, tid)) * ldb + uint32_t(chunk_col(j, tid) * 16);
     }
 
     // Slab row and (unswizzled) 16-byte chunk index of the lane's chunk j.
@@ -254,11 +284,16 @@ struct Slab {
                                                  nrec(it), kBufferFlags);
     }
 
-    // The same descriptor as four scalar words (base, stride 0, records, flags).
-    __device__ __forceinline__ i32x4 desc(int it) const {
-        const uint64_t addr = reinterpret_cast<uint64_t>(base + (int64_t)it * step);
-        return i32x4{uni(int(uint32_t(addr))), uni(int(uint32_t(addr >> 32) & 0xffffu)), uni(nrec(it)),
-                     kBufferFlags};
+    // The next slab's descriptor as four scalar words (base, stride 0, records,
+    // flags), kept up by additions: the products it * step cost more scalar
+    // instructions a slab than everything else the loop does on the scalar side.
+    __device__ __forceinline__ i32x4 next_desc() {
+        const uint32_t hi = uint32_t(uint64_t(left) >> 32);
+        const int nr = int32_t(hi) < 0 ? 0 : hi != 0 ? 0x7fffffff : int(min(uint32_t(left), 0x7fffffffu));
+        const i32x4 d = {uni(int(uint32_t(ahead))), uni(int(uint32_t(ahead >> 32) & 0xffffu)), uni(nr), kBufferFlags};
+        ahead += uint64_t(step);
+        left -= step;
+        return d;
     }
 
     // Elements of the lane's chunk j inside the inner edge (VE when not at the edge).
@@ -272,27 +307,37 @@ struct Slab {
     // the leading dimension, or the next row) and are cleared once the chunk
     // has landed.  Only a chunk that reaches past the operand's end needs the
     // element-by-element path.
-    __device__ __forceinline__ bool whole(int j, uint32_t nr) const { return voff[j] + 16u <= nr; }
+    static __device__ __forceinline__ bool whole(uint32_t off, uint32_t nr) { return off + 16u <= nr; }
 
-    // Issue the direct-to-LDS loads of iteration `it` (counted from kbeg), whose
-    // first k is k0, into the stage at `lds`.  EDGE = false: the caller knows
-    // the slab is wholly inside the inner edge (no per-chunk checks).
+    // Descriptor of the next slab, whose first k is k0, with the lane's chunk
+    // offsets in voff.  EDGE = false: the slab is
+    // wholly inside the inner edge and voff is as init left it; a checked slab
+    // recomputes voff with the chunks to skip out of range (once checked, a
+    // segment's remaining slabs are all checked).
     template <bool EDGE>
-    __device__ __forceinline__ void issue(int it, int k0, int K, int o0, int dout, unsigned char* lds,
-                                          int tid) const {
-        const i32x4 d = desc(it);
-        const bool tail = EDGE && (KC ? (k0 + BK > K) : (o0 + R > dout));
-        const int lim = KC ? (K - k0) : (dout - o0);
-        const int w = uni(tid >> 6);
+    __device__ __forceinline__ i32x4 prepare(int k0, int K, int o0, int dout, int tid) {
+        const i32x4 d = next_desc();
+        if constexpr (EDGE) {
+            tid = opaque(tid);
+            const bool tail = KC ? (k0 + BK > K) : (o0 + R > dout);
+            const int lim = KC ? (K - k0) : (dout - o0);
 #pragma unroll
-        for (int j = 0; j < PER_WAVE; ++j) {
-            uint32_t off = voff[j];
-            if constexpr (EDGE) {
+            for (int j = 0; j < PER_WAVE; ++j) {
                 const int kp = keep(j, tail, lim, tid);
-                if (kp == 0 || (kp < VE && !whole(j, uint32_t(d[2])))) off = 0x80000000u;
+                voff[j] = chunk_off(j, tid);
+                if (kp == 0 || (kp < VE && !whole(voff[j], uint32_t(d[2])))) voff[j] = 0x80000000u;
             }
-            dma16(d, off, lds_addr(lds + (w + j * NW) * 1024));
         }
+        return d;
+    }
+
+    // Issue the direct-to-LDS loads of one slab into the stage at LDS address `lds`.
+    template <bool EDGE>
+    __device__ __forceinline__ void issue(int k0, int K, int o0, int dout, uint32_t lds, int tid) {
+        const i32x4 d = prepare<EDGE>(k0, K, o0, dout, tid);
+        lds += uint32_t(uni(tid >> 6)) * 1024;
+#pragma unroll
+        for (int j = 0; j < PER_WAVE; ++j) dma16(d, voff[j], lds + j * NW * 1024);
     }
 
     // After the stage's loads have landed: clear the bytes past the edge of
@@ -309,10 +354,11 @@ struct Slab {
 #pragma unroll
         for (int j = 0; j < PER_WAVE; ++j) {
             const int kp = keep(j, tail, lim, tid);
+            const uint32_t at = chunk_off(j, tid);
             // a chunk that starts past the operand's end has landed as zeros
-            if (kp > 0 && kp < VE && voff[j] < nr) {
+            if (kp > 0 && kp < VE && at < nr) {
                 unsigned char* dst = lds + (w + j * NW) * 1024 + lane * 16;
-                if (whole(j, nr)) {
+                if (whole(at, nr)) {
                     u32x4 v = *reinterpret_cast<const u32x4*>(dst);
                     const int nb = kp * EB;   // bytes inside the edge
 #pragma unroll
@@ -330,7 +376,7 @@ struct Slab {
                 // loaded too (zero past the operand's end) and replaced by
                 // zero.
                 const __amdgpu_buffer_rsrc_t rs = rsrc(it);
-                const int off = int(voff[j]);
+                const int off = int(at);
 #pragma unroll 1
                 for (int e = 0; e < VE; ++e) {
                     // the loads return raw bits (unsigned integers of the element's width)
@@ -374,6 +420,7 @@ struct ConvSlab {
     using S_ = Slab<EB, R, BK, true, THREADS>;   // the same chunk placement as a K-contiguous GEMM slab
 
     int hb[PER_WAVE], wb[PER_WAVE], ib[PER_WAVE];   // per chunk: first input row / column of the window, image * H
+    uint32_t voff[PER_WAVE];                        // byte offsets of the prepared slab's chunks
     const unsigned char* x;
     uint32_t bytes;
     int H, W, C, S, dil_h, dil_w;
@@ -404,20 +451,26 @@ struct ConvSlab {
 
     // Slab of reduction indices [k0, k0 + BK): filter tap k0 / C, channels k0 mod C on.
     template <bool EDGE>
-    __device__ __forceinline__ void issue(int, int k0, int, int, int, unsigned char* lds, int tid) const {
+    __device__ __forceinline__ i32x4 prepare(int k0, int, int, int, int tid) {
         const int rs = k0 / C, c0 = k0 - rs * C;
         const int r = rs / S, s = rs - r * S;
-        const i32x4 d = {uni(int(uint32_t(reinterpret_cast<uint64_t>(x)))),
-                         uni(int(uint32_t(reinterpret_cast<uint64_t>(x) >> 32) & 0xffffu)), int(bytes), kBufferFlags};
-        const int w = uni(tid >> 6);
 #pragma unroll
         for (int j = 0; j < PER_WAVE; ++j) {
             const int h = hb[j] + r * dil_h, ww = wb[j] + s * dil_w;
-            uint32_t off = 0x80000000u;
+            voff[j] = 0x80000000u;
             if (uint32_t(h) < uint32_t(H) && uint32_t(ww) < uint32_t(W))
-                off = uint32_t((((ib[j] + h) * W + ww) * C + c0 + S_::chunk_col(j, tid) * VE) * EB);
-            dma16(d, off, lds_addr(lds + (w + j * NW) * 1024));
+                voff[j] = uint32_t((((ib[j] + h) * W + ww) * C + c0 + S_::chunk_col(j, tid) * VE) * EB);
         }
+        return i32x4{uni(int(uint32_t(reinterpret_cast<uint64_t>(x)))),
+                     uni(int(uint32_t(reinterpret_cast<uint64_t>(x) >> 32) & 0xffffu)), int(bytes), kBufferFlags};
+    }
+
+    template <bool EDGE>
+    __device__ __forceinline__ void issue(int k0, int K, int o0, int dout, uint32_t lds, int tid) {
+        const i32x4 d = prepare<EDGE>(k0, K, o0, dout, tid);
+        lds += uint32_t(uni(tid >> 6)) * 1024;
+#pragma unroll
+        for (int j = 0; j < PER_WAVE; ++j) dma16(d, voff[j], lds + j * NW * 1024);
     }
 
     // Convolution slabs have no ragged inner edge: nothing to fix.
@@ -427,9 +480,9 @@ struct ConvSlab {
 // ------------------------------------------------------------------ LDS fragment reads
 
 // 16 bytes = 8 k-values of one row of a K-contiguous slab, chunk q (0..7).
-template <int ROWB>
+template <int EB, int ROWB>
 __device__ __forceinline__ u32x4 lds_row_chunk(const unsigned char* lds, int row, int q) {
-    return *reinterpret_cast<const u32x4*>(lds + row * ROWB + ((q ^ swz<2, true, ROWB>(row)) << 4));
+    return *reinterpret_cast<const u32x4*>(lds + row * ROWB + ((q ^ swz<EB, true, ROWB>(row)) << 4));
 }
 
 // Byte address of element (k, col) of an MN-contiguous slab with ROWB-byte rows.
@@ -439,21 +492,23 @@ __device__ __forceinline__ int mn_addr(int k, int col) {
     return k * ROWB + (((col / VE) ^ swz<EB, false, ROWB>(k)) << 4) + (col % VE) * EB;
 }
 
-// Eight consecutive k (kb .. kb+7) of column (ob + lane % 32) of an MN-contiguous
-// 16-bit slab, via two LDS transpose reads of four k each.  Within each group
-// of 16 lanes the transpose read returns, to lane i, element i mod 4 of the
-// 8-byte words fetched by lanes 4e + i / 4 (e = 0..3); so lane j of the group
-// fetches row kb + j / 4, columns 4 (j mod 4) .. +3 of its 16-column half.
-template <int ROWB>
-__device__ __forceinline__ u32x4 lds_tr16(const unsigned char* lds, int kb, int ob, int lane) {
-    const int sub = lane & 15, h = lane >> 4;
-    const int col = ob + 16 * (h & 1) + 4 * (sub & 3);
-    const int k = kb + (sub >> 2);
+// Eight consecutive k (32 step + 8 (lane / 16) ..) of column (ob + 16 I + lane % 16)
+// of an MN-contiguous 16-bit slab, via two LDS transpose reads of four k each.
+// Within each group of 16 lanes the transpose read returns, to lane i, element
+// i mod 4 of the 8-byte words fetched by lanes 4e + i / 4 (e = 0..3); so lane j
+// of the group fetches row k + j / 4, columns 4 (j mod 4) .. +3.  The swizzle
+// flips bits of the chunk index, and 16 I is two chunks times I: block I's
+// address is block 0's with those bits flipped (ob must be a multiple of the
+// next power of two above the wave's columns), so one address serves them all.
+template <int ROWB, int I>
+__device__ __forceinline__ u32x4 lds_tr16(const unsigned char* lds, int step, int ob, int lane) {
+    const int sub = lane & 15;
     typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
-    lds_i16x4* p0 = (lds_i16x4*)(lds + mn_addr<2, ROWB>(k, col));
-    lds_i16x4* p1 = (lds_i16x4*)(lds + mn_addr<2, ROWB>(k + 4, col));
-    const i16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p0);
-    const i16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p1);
+    const uint32_t at = (uint32_t(size_t((lds_void*)lds)) +
+                         uint32_t(mn_addr<2, ROWB>(8 * (lane >> 4) + (sub >> 2), ob + 4 * (sub & 3)))) ^ uint32_t(32 * I);
+    lds_i16x4* p = (lds_i16x4*)(at + uint32_t(32 * step * ROWB));
+    const i16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p);
+    const i16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(at + uint32_t((32 * step + 4) * ROWB)));
     const u32x2 a = __builtin_bit_cast(u32x2, v0);
     const u32x2 b = __builtin_bit_cast(u32x2, v1);
     return u32x4{a.x, a.y, b.x, b.y};
@@ -462,12 +517,12 @@ __device__ __forceinline__ u32x4 lds_tr16(const unsigned char* lds, int kb, int 
 // ------------------------------------------------------------------ MFMA
 
 template <int DT>
-__device__ __forceinline__ f32x16 mfma16(const u32x4& a, const u32x4& b, const f32x16& c) {
+__device__ __forceinline__ f32x4 mfma16(const u32x4& a, const u32x4& b, const f32x4& c) {
     if constexpr (DT == DT_BF16) {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                        __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     } else {
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a),
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a),
                                                       __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
     }
 }
@@ -582,7 +637,8 @@ template <int DT, bool AKC, bool BKC, int V>
 struct Gemm {
     using C_ = Cfg<DT, V>;
     static constexpr int EB = C_::EB, BM = C_::BM, BN = C_::BN, BK = C_::BK;
-    static constexpr int WM = C_::WM, WN = C_::WN, THREADS = 64 * WM * WN, NW = WM * WN;
+    static constexpr int WM = C_::WM, WN = C_::WN, WK = WkOf<C_>::value, NW = WM * WN * WK, THREADS = 64 * NW;
+    static constexpr int BLOCK_THREADS = 64 * WM * WN;    // threads that hold the tile once (of WK copies)
     static constexpr int WTM = BM / WM, WTN = BN / WN;    // wave tile
     static constexpr int FM = WTM / 32, FN = WTN / 32;    // 32x32 MFMA blocks per wave
     static constexpr bool CONV = ConvOf<C_>::value;
@@ -612,12 +668,14 @@ struct Gemm {
         }
     };
 
-    // FP32 accumulators: one 32x32 MFMA block per (i, j).  FP64: four 16x16
-    // MFMA blocks per 32x32 block (q = 2 * row half + column half), so bands
-    // and blocks cover the same rows and columns for every type.
+    // Accumulators of one 32x32 block (i, j): one 32x32 MFMA block (FP32, FP8)
+    // or four 16x16 ones (16-bit types and FP64; q = 2 * row half + column
+    // half), so bands and blocks cover the same rows and columns for every type.
+    static constexpr bool kHalf = DT == DT_BF16 || DT == DT_F16;
     struct Acc32 { f32x16 v[FM][FN]; };
+    struct Acc16 { f32x4 v[FM][FN][4]; };
     struct Acc64 { f64x4 v[FM][FN][4]; };
-    using Acc = typename Pick<DT == DT_F64, Acc64, Acc32>::type;
+    using Acc = typename Pick<DT == DT_F64, Acc64, typename Pick<kHalf, Acc16, Acc32>::type>::type;
     // 16-byte chunks of one block's accumulators per lane (partial tiles are
     // stored and read in this fragment order)
     static constexpr int CPB = DT == DT_F64 ? 8 : 4;
@@ -629,6 +687,8 @@ struct Gemm {
             const f64x4& b = acc.v[i][j][r >> 1];
             const f64x2 v = (r & 1) ? f64x2{b[2], b[3]} : f64x2{b[0], b[1]};
             return __builtin_bit_cast(u32x4, v);
+        } else if constexpr (kHalf) {
+            return __builtin_bit_cast(u32x4, acc.v[i][j][r]);
         } else {
             const f32x4 v = {acc.v[i][j][4 * r], acc.v[i][j][4 * r + 1], acc.v[i][j][4 * r + 2],
                              acc.v[i][j][4 * r + 3]};
@@ -639,8 +699,9 @@ struct Gemm {
     // One block's worth of partial sums kept apart from the accumulators (the
     // running sum of the contributors ahead of this one in the split fix-up).
     struct Blk32 { f32x16 v; };
+    struct Blk16 { f32x4 q[4]; };
     struct Blk64 { f64x4 q[4]; };
-    using Blk = typename Pick<DT == DT_F64, Blk64, Blk32>::type;
+    using Blk = typename Pick<DT == DT_F64, Blk64, typename Pick<kHalf, Blk16, Blk32>::type>::type;
 
     // T chunk r = bits (first) or T chunk r += bits
     static __device__ __forceinline__ void blk_take_chunk(Blk& T, int r, const u32x4& bits, bool first) {
@@ -650,6 +711,10 @@ struct Gemm {
             const int o = (r & 1) * 2;
             b[o] = first ? v.x : b[o] + v.x;
             b[o + 1] = first ? v.y : b[o + 1] + v.y;
+        } else if constexpr (kHalf) {
+            const f32x4 v = __builtin_bit_cast(f32x4, bits);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) T.q[r][e] = first ? v[e] : T.q[r][e] + v[e];
         } else {
             const f32x4 v = __builtin_bit_cast(f32x4, bits);
             T.v[4 * r] = first ? v.x : T.v[4 * r] + v.x;
@@ -661,7 +726,7 @@ struct Gemm {
 
     // block (i, j) of acc = T + block (i, j)
     static __device__ __forceinline__ void acc_add_blk(Acc& acc, int i, int j, const Blk& T) {
-        if constexpr (DT == DT_F64) {
+        if constexpr (DT == DT_F64 || kHalf) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) acc.v[i][j][q] = T.q[q] + acc.v[i][j][q];
         } else {
@@ -680,6 +745,8 @@ struct Gemm {
                 b[0] += v.x;
                 b[1] += v.y;
             }
+        } else if constexpr (kHalf) {
+            acc.v[i][j][r] += __builtin_bit_cast(f32x4, bits);
         } else {
             const f32x4 v = __builtin_bit_cast(f32x4, bits);
             acc.v[i][j][4 * r] += v.x;
@@ -693,59 +760,8 @@ struct Gemm {
     static __device__ __forceinline__ void compute(const unsigned char* As, const unsigned char* Bs,
                                                    Acc& acc, int wm, int wn, int lane) {
         const int g = lane >> 5, l32 = lane & 31;
-        if constexpr (DT == DT_BF16 || DT == DT_F16) {
-            // Fragments are double-buffered across the k16 steps: the reads of
-            // step s+1 are interleaved between the MFMAs of step s, so LDS
-            // latency hides behind matrix work instead of stalling it.
-            constexpr int KS = BK / 16;
-            u32x4 af[2][FM], bf[2][FN];
-            auto load = [&](int s, int buf) {
-#pragma unroll
-                for (int i = 0; i < FM; ++i) {
-                    if constexpr (AKC) af[buf][i] = lds_row_chunk<SA::ROWB>(As, wm * WTM + i * 32 + l32, 2 * s + g);
-                    else af[buf][i] = lds_tr16<SA::ROWB>(As, 16 * s + 8 * g, wm * WTM + i * 32, lane);
-                }
-#pragma unroll
-                for (int j = 0; j < FN; ++j) {
-                    if constexpr (BKC) bf[buf][j] = lds_row_chunk<SB::ROWB>(Bs, wn * WTN + j * 32 + l32, 2 * s + g);
-                    else bf[buf][j] = lds_tr16<SB::ROWB>(Bs, 16 * s + 8 * g, wn * WTN + j * 32, lane);
-                }
-            };
-            // LDS reads per step: one per K-contiguous fragment, two per
-            // transposed one
-            constexpr int READS = FM * (AKC ? 1 : 2) + FN * (BKC ? 1 : 2);
-            constexpr int MFMAS = FM * FN;
-            load(0, 0);
-            // PRIO (the 256x256 tile: two waves per SIMD from one workgroup):
-            // a raised priority while a wave is in its MFMA section lets it
-            // keep the matrix core busy ahead of the other wave's loads and
-            // barrier (measured +1.5-2.5 % on large shapes; neutral on the
-            // small tiles, which keep the default).
-            if constexpr (PrioOf<C_>::value) __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                const int cur = s & 1;
-                // The reads of step s+1 are interleaved one by one between
-                // the MFMAs of step s, which cover their latency; the group
-                // barriers fix that order (MFMA, read, MFMA, read, ...) and
-                // the closing barrier keeps the compiler from moving work
-                // across steps.
-                if (s + 1 < KS) load(s + 1, cur ^ 1);
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int j = 0; j < FN; ++j) acc.v[i][j] = mfma16<DT>(af[cur][i], bf[cur][j], acc.v[i][j]);
-                if (s + 1 < KS) {
-#pragma unroll
-                    for (int k = 0; k < READS || k < MFMAS; ++k) {
-                        if (k < MFMAS) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-                        if (k < READS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if constexpr (PrioOf<C_>::value) __builtin_amdgcn_s_setprio(0);
-        } else if constexpr (DT == DT_F64) {
+        static_assert(!kHalf, "16-bit types run slab_loop");
+        if constexpr (DT == DT_F64) {
             // v_mfma_f64_16x16x4f64: lane l holds A[row l%16][k l/16] and
             // B[k l/16][col l%16] of the k4 step; each 32x32 block is four
             // 16x16 MFMA blocks.
@@ -780,7 +796,7 @@ struct Gemm {
                 for (int i = 0; i < FM; ++i) {
                     const int row = wm * WTM + i * 32 + l32;
                     if constexpr (AKC) {
-                        af[i] = __builtin_bit_cast(f32x4, lds_row_chunk<SA::ROWB>(As, row, 2 * c + g));
+                        af[i] = __builtin_bit_cast(f32x4, lds_row_chunk<EB, SA::ROWB>(As, row, 2 * c + g));
                     } else {
 #pragma unroll
                         for (int u = 0; u < 4; ++u)
@@ -791,7 +807,7 @@ struct Gemm {
                 for (int j = 0; j < FN; ++j) {
                     const int col = wn * WTN + j * 32 + l32;
                     if constexpr (BKC) {
-                        bf[j] = __builtin_bit_cast(f32x4, lds_row_chunk<SB::ROWB>(Bs, col, 2 * c + g));
+                        bf[j] = __builtin_bit_cast(f32x4, lds_row_chunk<EB, SB::ROWB>(Bs, col, 2 * c + g));
                     } else {
 #pragma unroll
                         for (int u = 0; u < 4; ++u)
@@ -820,15 +836,15 @@ struct Gemm {
 #pragma unroll
                 for (int j = 0; j < FN; ++j) {
                     const int row = wn * WTN + j * 32 + l32;
-                    const u32x4 lo = lds_row_chunk<SB::ROWB>(Bs, row, 4 * s + 2 * g);
-                    const u32x4 hi = lds_row_chunk<SB::ROWB>(Bs, row, 4 * s + 2 * g + 1);
+                    const u32x4 lo = lds_row_chunk<EB, SB::ROWB>(Bs, row, 4 * s + 2 * g);
+                    const u32x4 hi = lds_row_chunk<EB, SB::ROWB>(Bs, row, 4 * s + 2 * g + 1);
                     bf[j] = i32x8{int(lo.x), int(lo.y), int(lo.z), int(lo.w), int(hi.x), int(hi.y), int(hi.z), int(hi.w)};
                 }
 #pragma unroll
                 for (int i = 0; i < FM; ++i) {
                     const int row = wm * WTM + i * 32 + l32;
-                    const u32x4 lo = lds_row_chunk<SA::ROWB>(As, row, 4 * s + 2 * g);
-                    const u32x4 hi = lds_row_chunk<SA::ROWB>(As, row, 4 * s + 2 * g + 1);
+                    const u32x4 lo = lds_row_chunk<EB, SA::ROWB>(As, row, 4 * s + 2 * g);
+                    const u32x4 hi = lds_row_chunk<EB, SA::ROWB>(As, row, 4 * s + 2 * g + 1);
                     const i32x8 af = i32x8{int(lo.x), int(lo.y), int(lo.z), int(lo.w), int(hi.x), int(hi.y),
                                            int(hi.z), int(hi.w)};
 #pragma unroll
@@ -882,18 +898,18 @@ struct Gemm {
     // Slabs of iterations from kedge on are loaded with per-chunk checks
     // against the operands' inner edges (and fixed up once they have landed);
     // the others lie wholly inside them.
-    static __device__ __forceinline__ bool step(const Prob& a, const SA& sa, const SB& sb, int it, int kbeg,
+    static __device__ __forceinline__ bool step(const Prob& a, SA& sa, SB& sb, int it, int kbeg,
                                                 int kend, int kedge, int m0, int n0, unsigned char* cur,
                                                 unsigned char* nxt, unsigned char* fix, Acc& acc, int tid) {
         const int lane = tid & 63, w = tid >> 6, wm = w / WN, wn = w % WN;
         const int ahead = it + NS - 1;
         if (ahead < kend) {
             if (ahead < kedge) {
-                sa.template issue<false>(ahead - kbeg, ahead * BK, a.K, m0, a.M, nxt, tid);
-                sb.template issue<false>(ahead - kbeg, ahead * BK, a.K, n0, a.N, nxt + SA::BYTES, tid);
+                sa.template issue<false>(ahead * BK, a.K, m0, a.M, lds_addr(nxt), tid);
+                sb.template issue<false>(ahead * BK, a.K, n0, a.N, lds_addr(nxt) + SA::BYTES, tid);
             } else {
-                sa.template issue<true>(ahead - kbeg, ahead * BK, a.K, m0, a.M, nxt, tid);
-                sb.template issue<true>(ahead - kbeg, ahead * BK, a.K, n0, a.N, nxt + SA::BYTES, tid);
+                sa.template issue<true>(ahead * BK, a.K, m0, a.M, lds_addr(nxt), tid);
+                sb.template issue<true>(ahead * BK, a.K, n0, a.N, lds_addr(nxt) + SA::BYTES, tid);
             }
         }
         compute(cur, cur + SA::BYTES, acc, wm, wn, lane);
@@ -912,7 +928,7 @@ struct Gemm {
     // Iterations kk + U (U = 0 .. NS-1) of the pipeline, each on its own
     // stage; false once the last iteration has been consumed.
     template <int... U>
-    static __device__ __forceinline__ bool steps(const Prob& a, const SA& sa, const SB& sb, int kk, int kbeg,
+    static __device__ __forceinline__ bool steps(const Prob& a, SA& sa, SB& sb, int kk, int kbeg,
                                                  int kend, int kedge, int m0, int n0, const Stages& st, Acc& acc,
                                                  int tid, std::integer_sequence<int, U...>) {
         return (step(a, sa, sb, kk + U, kbeg, kend, kedge, m0, n0, st.template at<U>(),
@@ -922,26 +938,289 @@ struct Gemm {
 
     // Slab kbeg + J into stage J, checked from kedge on.
     template <int J>
-    static __device__ __forceinline__ void prologue_one(const Prob& a, const SA& sa, const SB& sb, int kbeg,
+    static __device__ __forceinline__ void prologue_one(const Prob& a, SA& sa, SB& sb, int kbeg,
                                                         int kend, int kedge, int m0, int n0, const Stages& st,
                                                         int tid) {
         const int it = kbeg + J;
         if (it >= kend) return;
         if (it < kedge) {
-            sa.template issue<false>(J, it * BK, a.K, m0, a.M, st.template at<J>(), tid);
-            sb.template issue<false>(J, it * BK, a.K, n0, a.N, st.template at<J>() + SA::BYTES, tid);
+            sa.template issue<false>(it * BK, a.K, m0, a.M, lds_addr(st.template at<J>()), tid);
+            sb.template issue<false>(it * BK, a.K, n0, a.N, lds_addr(st.template at<J>()) + SA::BYTES, tid);
         } else {
-            sa.template issue<true>(J, it * BK, a.K, m0, a.M, st.template at<J>(), tid);
-            sb.template issue<true>(J, it * BK, a.K, n0, a.N, st.template at<J>() + SA::BYTES, tid);
+            sa.template issue<true>(it * BK, a.K, m0, a.M, lds_addr(st.template at<J>()), tid);
+            sb.template issue<true>(it * BK, a.K, n0, a.N, lds_addr(st.template at<J>()) + SA::BYTES, tid);
         }
     }
 
     // Prologue: slab kbeg + J into stage J (J = 0 .. NS-2).
     template <int... J>
-    static __device__ __forceinline__ void prologue(const Prob& a, const SA& sa, const SB& sb, int kbeg, int kend,
+    static __device__ __forceinline__ void prologue(const Prob& a, SA& sa, SB& sb, int kbeg, int kend,
                                                     int kedge, int m0, int n0, const Stages& st, int tid,
                                                     std::integer_sequence<int, J...>) {
         (prologue_one<J>(a, sa, sb, kbeg, kend, kedge, m0, n0, st, tid), ...);
+    }
+
+    // ---- 16-bit types: fragments carried across the slab seam
+    //
+    // A wave's block is FA x FB blocks of 16x16.  A slab is two k32 steps.  In
+    // slot i of a step the wave runs the MFMAs of A fragment i with every B
+    // fragment, and then reads fragment i of the next step into the registers
+    // just freed; the B fragments, in use throughout a step, have two buffers.
+    // The second step of a slab runs behind the seam: once its fragments are
+    // in registers, every wave has read the whole slab, so after one barrier
+    // the next slab (landed before it) can be read, and the stage just consumed
+    // refilled, while the matrix cores work on that step.  The refill's loads
+    // are spread one by one between the MFMAs: issued in one burst ahead of
+    // them, the memory pipeline's queue kept the waves from their MFMAs.
+    static constexpr int FA = WTM / 16, FB = WTN / 16;
+    static constexpr bool kStream = kHalf && (WK > 1 || V == 5 || V == 6 || V == 7);
+    // Slot in which the last A fragment of the second step is read ahead, into
+    // a spare register set, so that the seam does not wait for it.
+    static constexpr int SPARE = FA > 4 ? FA - 3 : FA - 2;
+
+    // Slots of the second step over which the refill's loads are issued.
+    static constexpr int SPREAD = FA > 4 ? 8 : 1;
+
+    struct Frags { u32x4 a[FA], b[2][FB], spare; };
+
+    template <int I>
+    static __device__ __forceinline__ u32x4 read_a(int s, const unsigned char* As, int wm, int lane) {
+        if constexpr (AKC) return lds_row_chunk<EB, SA::ROWB>(As, wm * WTM + I * 16 + (lane & 15), 4 * s + (lane >> 4));
+        else return lds_tr16<SA::ROWB, I>(As, s, wm * WTM, lane);
+    }
+    template <int J>
+    static __device__ __forceinline__ u32x4 read_b(int s, const unsigned char* Bs, int wn, int lane) {
+        if constexpr (BKC) return lds_row_chunk<EB, SB::ROWB>(Bs, wn * WTN + J * 16 + (lane & 15), 4 * s + (lane >> 4));
+        else return lds_tr16<SB::ROWB, J>(Bs, s, wn * WTN, lane);
+    }
+    template <int J0, int J1>
+    static __device__ __forceinline__ void read_bs(Frags& f, int buf, int s, const unsigned char* Bs, int wn, int lane) {
+        if constexpr (J0 < J1) {
+            f.b[buf][J0] = read_b<J0>(s, Bs, wn, lane);
+            read_bs<J0 + 1, J1>(f, buf, s, Bs, wn, lane);
+        }
+    }
+    template <int... I>
+    static __device__ __forceinline__ void read_as(Frags& f, int s, const unsigned char* As, int wm, int lane,
+                                                   std::integer_sequence<int, I...>) {
+        ((f.a[I] = read_a<I>(s, As, wm, lane)), ...);
+    }
+
+    // The refill of one stage: descriptors of both slabs (their chunk offsets
+    // are the slabs' own).
+    struct Refill {
+        i32x4 da, db;
+        uint32_t lds;                      // LDS address of this wave's first block
+    };
+
+    template <int J>
+    static __device__ __forceinline__ void refill_one(const Refill& rf, const SA& sa, const SB& sb) {
+        if constexpr (J < SB::PER_WAVE) dma16_at<SA::BYTES + J * NW * 1024>(rf.db, sb.voff[J], rf.lds);
+        else dma16_at<(J - SB::PER_WAVE) * NW * 1024>(rf.da, sa.voff[J - SB::PER_WAVE], rf.lds);
+    }
+    template <int J0, int J1>
+    static __device__ __forceinline__ void refill_range(const Refill& rf, const SA& sa, const SB& sb) {
+        if constexpr (J0 < J1) {
+            refill_one<J0>(rf, sa, sb);
+            refill_range<J0 + 1, J1>(rf, sa, sb);
+        }
+    }
+
+    // Slot I of step S; the fragments of the other step are read from the
+    // slab at As / Bs.  The scheduling barrier fixes the order.
+    template <int I, int S, bool REFILL>
+    static __device__ __forceinline__ void slot(Frags& f, const unsigned char* As, const unsigned char* Bs, Acc& acc,
+                                                const Refill& rf, const SA& sa, const SB& sb, int wm, int wn,
+                                                int lane) {
+        if constexpr (REFILL && I < SPREAD) refill_range<I * LOADS / SPREAD, (I + 1) * LOADS / SPREAD>(rf, sa, sb);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < FB; ++j) {
+            f32x4& c = acc.v[I / 2][j / 2][2 * (I & 1) + (j & 1)];
+            c = mfma16<DT>(f.a[I], f.b[S][j], c);
+        }
+        if constexpr (S == 0 && I == SPARE) f.spare = read_a<FA - 1>(1, As, wm, lane);
+        if constexpr (S == 0 && I == FA - 1) f.a[I] = f.spare;
+        else f.a[I] = read_a<I>(S ^ 1, As, wm, lane);
+        // the B fragments in the first half of the step
+        constexpr int H = FA / 2;
+        if constexpr (I < H) read_bs<I * FB / H, (I + 1) * FB / H>(f, S ^ 1, S ^ 1, Bs, wn, lane);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    template <int S, bool REFILL, int... I>
+    static __device__ __forceinline__ void half_slab(Frags& f, const unsigned char* As, const unsigned char* Bs,
+                                                     Acc& acc, const Refill& rf, const SA& sa, const SB& sb, int wm,
+                                                     int wn, int lane,
+                                                     std::integer_sequence<int, I...>) {
+        (slot<I, S, REFILL>(f, As, Bs, acc, rf, sa, sb, wm, wn, lane), ...);
+    }
+
+    // Refill of the stage at `lds` with slab `it`.
+    static __device__ __forceinline__ void prep_refill(Refill& rf, const Prob& a, SA& sa, SB& sb, int it, int kbeg,
+                                                       int kedge, int m0, int n0, uint32_t lds, int tid) {
+        rf.lds = lds;
+        if (it >= kedge) {
+            rf.da = sa.template prepare<true>(it * BK, a.K, m0, a.M, tid);
+            rf.db = sb.template prepare<true>(it * BK, a.K, n0, a.N, tid);
+        } else {
+            rf.da = sa.template prepare<false>(it * BK, a.K, m0, a.M, tid);
+            rf.db = sb.template prepare<false>(it * BK, a.K, n0, a.N, tid);
+        }
+    }
+
+    // Slabs [kbeg, kend), the first NS - 1 of them in flight, the first
+    // landed: a loop that refills each stage once it is consumed, and one for
+    // the slabs with nothing left to refill (loads past the end, masked out or
+    // through empty descriptors, cost 0.3-0.5 us at the end of a segment; a
+    // branch around each, 2-5 %).  The stages lie one after another in LDS and
+    // are picked by offset: one copy of each body and one way through it keep the
+    // accumulators in place.
+    static __device__ __forceinline__ void slab_loop(const Prob& a, SA& sa, SB& sb, int kbeg, int kend, int kedge,
+                                                     int m0, int n0, const Stages& st, Acc& acc, int tid) {
+        static_assert(BK == 64 && FA >= 4 && FB >= 2 && WK == 1, "two k32 steps a slab");
+        using Slots = std::make_integer_sequence<int, FA>;
+        const int lane = tid & 63, w = uni(tid >> 6), wm = (tid >> 6) / WN, wn = (tid >> 6) % WN;
+        const uint32_t dst = lds_addr(st.template at<0>()) + w * 1024;
+        unsigned char* const lds = st.template at<0>();
+        Frags f;
+        Refill rf;
+        read_bs<0, FB>(f, 0, 0, lds + SA::BYTES, wn, lane);
+        read_as(f, 0, lds, wm, lane, Slots{});
+        if (kbeg + NS - 1 < kend) {
+            prep_refill(rf, a, sa, sb, kbeg + NS - 1, kbeg, kedge, m0, n0, dst + (NS - 1) * STAGE, tid);
+            refill_range<0, LOADS>(rf, sa, sb);
+        }
+        int cur = 0;                       // byte offset of the stage of slab `it`
+        int it = kbeg;
+        for (; it + NS < kend; ++it) {
+            half_slab<0, false>(f, lds + cur, lds + cur + SA::BYTES, acc, rf, sa, sb, wm, wn, lane, Slots{});
+            const int nxt = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
+            wait_vmem_le<LOADS * (NS - 2)>();
+            if (it + 1 >= kedge) fix_slab(a, sa, sb, it + 1, kbeg, m0, n0, lds + nxt, tid);
+            step_barrier();
+            prep_refill(rf, a, sa, sb, it + NS, kbeg, kedge, m0, n0, dst + cur, tid);
+            half_slab<1, true>(f, lds + nxt, lds + nxt + SA::BYTES, acc, rf, sa, sb, wm, wn, lane, Slots{});
+            cur = nxt;
+        }
+        for (; it < kend; ++it) {
+            half_slab<0, false>(f, lds + cur, lds + cur + SA::BYTES, acc, rf, sa, sb, wm, wn, lane, Slots{});
+            const int nxt = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
+            wait_slab(kend - 2 - it);
+            if (it + 1 >= kedge && it + 1 < kend) fix_slab(a, sa, sb, it + 1, kbeg, m0, n0, lds + nxt, tid);
+            step_barrier();
+            // (behind the last slab the fragments read here are never used)
+            half_slab<1, false>(f, lds + nxt, lds + nxt + SA::BYTES, acc, rf, sa, sb, wm, wn, lane, Slots{});
+            cur = nxt;
+        }
+        // Every wave has read the last slab before the last barrier.
+    }
+
+    static __device__ __forceinline__ void fix_slab(const Prob& a, const SA& sa, const SB& sb, int it, int kbeg, int m0,
+                                                    int n0, unsigned char* stage, int tid) {
+        sa.fix_edge(it - kbeg, it * BK, a.K, m0, a.M, stage, tid);
+        sb.fix_edge(it - kbeg, it * BK, a.K, n0, a.N, stage + SA::BYTES, tid);
+    }
+
+    template <int... I, int... J>
+    static __device__ __forceinline__ void read_frags(u32x4 (&af)[FA], u32x4 (&bf)[FB], int s, const unsigned char* stage,
+                                                      int wm, int wn, int lane, std::integer_sequence<int, I...>,
+                                                      std::integer_sequence<int, J...>) {
+        ((bf[J] = read_b<J>(s, stage + SA::BYTES, wn, lane)), ...);
+        ((af[I] = read_a<I>(s, stage, wm, lane)), ...);
+    }
+
+    static __device__ __forceinline__ void issue_a(const Prob& a, SA& sa, bool edge, int it, int m0, uint32_t lds, int tid) {
+        if (edge) sa.template issue<true>(it * BK, a.K, m0, a.M, lds, tid);
+        else sa.template issue<false>(it * BK, a.K, m0, a.M, lds, tid);
+    }
+    static __device__ __forceinline__ void issue_b(const Prob& a, SB& sb, bool edge, int it, int n0, uint32_t lds, int tid) {
+        if (edge) sb.template issue<true>(it * BK, a.K, n0, a.N, lds, tid);
+        else sb.template issue<false>(it * BK, a.K, n0, a.N, lds, tid);
+    }
+
+    // ---- streaming tiles (WK waves split the slab's k) and the 64-row and
+    // 64-column ones
+    //
+    // Bound by the bytes in flight from HBM, not by the matrix cores: a slab is
+    // waited for, and the stage consumed before it refilled at once, so NS - 1
+    // slabs are in flight while one is consumed.
+    static __device__ __forceinline__ void stream_loop(const Prob& a, SA& sa, SB& sb, int kbeg, int kend, int kedge,
+                                                       int m0, int n0, const Stages& st, Acc& acc, int tid) {
+        constexpr int STEPS = BK / 32 / WK;    // k32 steps of a wave in a slab
+        const int lane = tid & 63, w = tid >> 6, wk = uni(w / (WM * WN)), wm = w % (WM * WN) / WN, wn = w % WN;
+        unsigned char* const lds = st.template at<0>();
+        const uint32_t dst = lds_addr(st.template at<0>());
+        int cur = 0, free = (NS - 1) * STAGE;
+        for (int it = kbeg; it < kend; ++it) {
+            wait_slab(min(NS - 2, kend - 1 - it));
+            if (it >= kedge) {
+                sa.fix_edge(it - kbeg, it * BK, a.K, m0, a.M, lds + cur, tid);
+                sb.fix_edge(it - kbeg, it * BK, a.K, n0, a.N, lds + cur + SA::BYTES, tid);
+            }
+            step_barrier();
+            const int ahead = it + NS - 1;
+            if (ahead < kend) {
+                // the operand with more rows, the one that streams from HBM, first
+                const bool edge = ahead >= kedge;
+                if constexpr (BM > BN) issue_a(a, sa, edge, ahead, m0, dst + free, tid);
+                issue_b(a, sb, edge, ahead, n0, dst + free + SA::BYTES, tid);
+                if constexpr (BM <= BN) issue_a(a, sa, edge, ahead, m0, dst + free, tid);
+            }
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) {
+                u32x4 af[FA], bf[FB];
+                read_frags(af, bf, wk * STEPS + s, lds + cur, wm, wn, lane, std::make_integer_sequence<int, FA>{},
+                           std::make_integer_sequence<int, FB>{});
+#pragma unroll
+                for (int i = 0; i < FA; ++i)
+#pragma unroll
+                    for (int j = 0; j < FB; ++j) {
+                        f32x4& c = acc.v[i / 2][j / 2][2 * (i & 1) + (j & 1)];
+                        c = mfma16<DT>(af[i], bf[j], c);
+                    }
+            }
+            free = cur;
+            cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
+        }
+        step_barrier();
+        if constexpr (WK > 1) add_waves(lds, acc, wk, lane, std::make_integer_sequence<int, FM>{});
+        else step_barrier();
+    }
+
+    // Band I of the tile (its 32-row blocks) is added up by wave I mod WK, from
+    // the copies of the waves after it in turn.
+    template <int I>
+    static __device__ __forceinline__ unsigned char* copy_at(unsigned char* lds, int j, int slot, int r, int lane) {
+        return lds + (((I * FN + j) * (WK - 1) + slot) * 4 + r) * 1024 + lane * 16;
+    }
+    template <int I>
+    static __device__ __forceinline__ void put_band(unsigned char* lds, const Acc& acc, int wk, int lane) {
+        const int slot = (wk + 2 * WK - I - 1) % WK;     // WK - 1 for the band's own wave
+        if (slot == WK - 1) return;
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) *reinterpret_cast<f32x4*>(copy_at<I>(lds, j, slot, r, lane)) = acc.v[I][j][r];
+    }
+    template <int I>
+    static __device__ __forceinline__ void add_band(unsigned char* lds, Acc& acc, int wk, int lane) {
+        if (I % WK != wk) return;
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int slot = 0; slot < WK - 1; ++slot)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    acc.v[I][j][r] += *reinterpret_cast<const f32x4*>(copy_at<I>(lds, j, slot, r, lane));
+    }
+    template <int... I>
+    static __device__ __forceinline__ void add_waves(unsigned char* lds, Acc& acc, int wk, int lane,
+                                                     std::integer_sequence<int, I...>) {
+        step_barrier();
+        (put_band<I>(lds, acc, wk, lane), ...);
+        step_barrier();
+        (add_band<I>(lds, acc, wk, lane), ...);
+        step_barrier();
     }
 
     // Iterations [kbeg, kend) of a tile: the first NS - 1 slabs are loaded
@@ -959,15 +1238,25 @@ struct Gemm {
         sb.init(a.B, a.ldb, n0, a.N, kbeg, a.K, tid);
         __syncthreads();   // LDS may still be in use (previous epilogue or loop)
         prologue(a, sa, sb, kbeg, kend, kedge, m0, n0, st, tid, std::make_integer_sequence<int, NS - 1>{});
+        if constexpr (kStream) {
+            stream_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, tid);
+            return;
+        }
         wait_slab(min(NS - 2, kend - 1 - kbeg));
         if (kbeg >= kedge) {
             sa.fix_edge(0, kbeg * BK, a.K, m0, a.M, st.template at<0>(), tid);
             sb.fix_edge(0, kbeg * BK, a.K, n0, a.N, st.template at<0>() + SA::BYTES, tid);
         }
         step_barrier();
-        for (int kk = kbeg;; kk += NS)
-            if (!steps(a, sa, sb, kk, kbeg, kend, kedge, m0, n0, st, acc, tid, std::make_integer_sequence<int, NS>{}))
-                return;
+        if constexpr (kStream) {
+        } else if constexpr (kHalf) {
+            slab_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, tid);
+        } else {
+            for (int kk = kbeg;; kk += NS)
+                if (!steps(a, sa, sb, kk, kbeg, kend, kedge, m0, n0, st, acc, tid,
+                           std::make_integer_sequence<int, NS>{}))
+                    return;
+        }
     }
 
     // MAC-loop iterations [klo, khi) of one tile into acc (zeroed first).
@@ -987,6 +1276,9 @@ struct Gemm {
                 if constexpr (DT == DT_F64) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) acc.v[i][j][q] = f64x4{0, 0, 0, 0};
+                } else if constexpr (kHalf) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc.v[i][j][q] = f32x4{0, 0, 0, 0};
                 } else {
                     acc.v[i][j] = f32x16{0};
                 }
@@ -1144,9 +1436,13 @@ struct Gemm {
     // the registers); REDUCERS caps the reducing contributors.
     static constexpr bool kBlockUnits = FM < 4;
     static constexpr int REDUCERS = kBlockUnits ? UNITS : FM;
-    static constexpr int EPI_LD = WTN + 8;                     // staged rows: one band wide
+    // staged rows: one band wide, padded so that the lane groups of one
+    // store, four rows apart, fall on distinct banks (two groups of 32 columns,
+    // or four of 16)
+    static constexpr int EPI_LD = WTN + (kHalf ? 4 : 8);
     static constexpr int EPI_BYTES = 32 * EPI_LD * 4;
     static constexpr int EPI_PER_STAGE = STAGE / EPI_BYTES;    // waves staging in one LDS stage
+    static_assert(WK == 1 || UNITS * (WK - 1) * 4096 <= NS * STAGE, "the waves' copies must fit in the stages");
     static_assert(EPI_PER_STAGE >= 1 && NW <= EPI_PER_STAGE * NS, "epilogue staging must fit in the stages");
     static_assert(UNITS <= 16 && REDUCERS <= 8, "unit masks and flag words");
 
@@ -1160,8 +1456,8 @@ struct Gemm {
                                                      int tid) {
 #pragma unroll
         for (int r = 0; r < CPB; ++r)
-            buf[r] = __builtin_amdgcn_raw_buffer_load_b128(rs, (((i * FN + j) * CPB + r) * THREADS + tid) * 16, 0,
-                                                           kCoherent);
+            buf[r] = __builtin_amdgcn_raw_buffer_load_b128(
+                rs, (((i * FN + j) * CPB + r) * BLOCK_THREADS + tid % BLOCK_THREADS) * 16, 0, kCoherent);
     }
 
     // Adds the copy of peer k (in buf) to the sum of unit (i, j).
@@ -1240,13 +1536,38 @@ struct Gemm {
         if (ts && tid == 0) ts[f] = __builtin_amdgcn_s_memtime();
     }
 
+    // Block (i, j) into staged rows at st, from the MFMA output layout.
+    static __device__ __forceinline__ void stage_block(float* st, const Acc& acc, int i, int j, int lane) {
+        if constexpr (kHalf) {
+            const int l16 = lane & 15, g = lane >> 4;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    st[((q >> 1) * 16 + 4 * g + e) * EPI_LD + (q & 1) * 16 + l16] = acc.v[i][j][q][e];
+        } else if constexpr (DT != DT_F64) {
+            const int l32 = lane & 31, g = lane >> 5;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st[(8 * (r >> 2) + 4 * g + (r & 3)) * EPI_LD + l32] = acc.v[i][j][r];
+        }
+    }
+
     static __device__ __forceinline__ void finish(const KArgs& ka, const Prob& a, int tile, Acc& acc, int tid,
                                                   const Stages& sts, int wg, const Exit& x, uint64_t* ts) {
         tid = opaque(tid);
-        const int lane = tid & 63, w = tid >> 6, wm = w / WN, wn = w % WN;
-        const int g = lane >> 5, l32 = lane & 31;
-        const int store_mask = uni(x.store_mask), fin_mask = uni(x.fin_mask);
-        if (store_mask) {
+        const int lane = tid & 63, w = tid >> 6, wm = w % (WM * WN) / WN, wn = w % WN;
+        int store_mask = uni(x.store_mask), fin_mask = uni(x.fin_mask);
+        const bool any_store = store_mask != 0, any_fin = fin_mask != 0;
+        if constexpr (WK > 1) {
+            // the bands this wave holds the sums of
+            int mine = 0;
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+                if (i % WK == uni(w)) mine |= ((1 << FN) - 1) << (i * FN);
+            store_mask &= mine;
+            fin_mask &= mine;
+        }
+        if (any_store) {
             const __amdgpu_buffer_rsrc_t own = slot_rsrc(ka.partials + (size_t)wg * SLOT);
 #pragma unroll
             for (int i = 0; i < FM; ++i)
@@ -1257,7 +1578,8 @@ struct Gemm {
                         for (int r = 0; r < CPB; ++r) {
                             const int q = (i * FN + j) * CPB + r;
                             __builtin_amdgcn_raw_buffer_store_b128(acc_chunk(acc, i, j, r), own,
-                                                                   (q * THREADS + tid) * 16, 0, kCoherent);
+                                                                   (q * BLOCK_THREADS + tid % BLOCK_THREADS) * 16,
+                                                                   0, kCoherent);
                         }
                     }
             wait_vmem();          // this wave's coherent partial stores have completed
@@ -1269,7 +1591,7 @@ struct Gemm {
             }
         }
         stamp(ts, 2, tid);
-        if (!fin_mask) {
+        if (!any_fin) {
             stamp(ts, 3, tid);
             return;
         }
@@ -1310,9 +1632,7 @@ struct Gemm {
 #pragma unroll
                 for (int j = 0; j < FN; ++j) {
                     if (peers) reduce_unit(ka, acc, i, j, lo, hi, wg, tid);
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        st[(8 * (r >> 2) + 4 * g + (r & 3)) * EPI_LD + j * 32 + l32] = acc.v[i][j][r];
+                    stage_block(st + j * 32, acc, i, j, lane);
                 }
                 constexpr int LPR = WTN / 8;
                 const int col = n0 + (lane % LPR) * 8;
@@ -1334,8 +1654,7 @@ struct Gemm {
                     if (peers) reduce_unit(ka, acc, i, j, lo, hi, wg, tid);
                     const int col = n0 + j * 32 + (lane % 4) * 8;
                     const int ncol = min(max(a.N - col, 0), 8);
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) st[(8 * (r >> 2) + 4 * g + (r & 3)) * EPI_LD + l32] = acc.v[i][j][r];
+                    stage_block(st, acc, i, j, lane);
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                     __builtin_amdgcn_wave_barrier();
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1575,29 +1894,16 @@ __global__ void __launch_bounds__((kThreadsOf<DT, V>)) __attribute__((amdgpu_wav
 skgemm_kernel(KArgs a) {
     using G = Gemm<DT, AKC, BKC, V>;
     constexpr int S = G::STAGE;
-    __shared__ __attribute__((aligned(1024))) unsigned char st0[S];
-    __shared__ __attribute__((aligned(1024))) unsigned char st1[S];
-    typename G::Stages sts{st0, st1, nullptr, nullptr, nullptr};
-    if constexpr (G::NS == 2) {
-        G::template run<FULL>(a, sts);
-    } else if constexpr (G::NS == 3) {
-        __shared__ __attribute__((aligned(1024))) unsigned char st2[S];
-        sts.s2 = st2;
-        G::template run<FULL>(a, sts);
-    } else if constexpr (G::NS == 4) {
-        __shared__ __attribute__((aligned(1024))) unsigned char st2[S];
-        __shared__ __attribute__((aligned(1024))) unsigned char st3[S];
-        sts.s2 = st2;
-        sts.s3 = st3;
+    if constexpr (G::kHalf) {
+        // one block: the 16-bit MAC loop picks its stages by offset
+        __shared__ __attribute__((aligned(1024))) unsigned char st[G::NS * S];
+        typename G::Stages sts{st, st + S, st + 2 * S, st + 3 * S, st + 4 * S};
         G::template run<FULL>(a, sts);
     } else {
-        static_assert(G::NS == 5, "2 to 5 pipeline stages");
-        __shared__ __attribute__((aligned(1024))) unsigned char st2[S];
-        __shared__ __attribute__((aligned(1024))) unsigned char st3[S];
-        __shared__ __attribute__((aligned(1024))) unsigned char st4[S];
-        sts.s2 = st2;
-        sts.s3 = st3;
-        sts.s4 = st4;
+        __shared__ __attribute__((aligned(1024))) unsigned char st0[S];
+        __shared__ __attribute__((aligned(1024))) unsigned char st1[S];
+        static_assert(G::NS == 2, "two stages");
+        typename G::Stages sts{st0, st1, nullptr, nullptr, nullptr};
         G::template run<FULL>(a, sts);
     }
 }
