@@ -57,6 +57,8 @@ const void* kernel_table(bool akc, bool bkc, int v) {
             case 7: return kc_only<DT, 7, FULL>(akc, bkc);     // tall tile, convolution
             case 8: return any_layout<DT, 8, FULL>(akc, bkc);  // small tile, three stages
             case 9: return kc_only<DT, 9, FULL>(akc, bkc);     // the same, convolution
+            case 10: return kc_only<DT, 10, FULL>(akc, bkc);   // streaming tiles
+            case 11: return kc_only<DT, 11, FULL>(akc, bkc);
             default: return nullptr;
         }
     } else if constexpr (DT == DT_F8) {

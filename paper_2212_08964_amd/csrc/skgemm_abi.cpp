@@ -113,6 +113,8 @@ TileCfg tile_for(int dt, int v) {
     if (v == 5 && (dt == DT_BF16 || dt == DT_F16)) return kTile16K;     // skinny
     if ((v == 6 || v == 7) && (dt == DT_BF16 || dt == DT_F16)) return kTile16T;     // tall
     if ((v == kVariantDeep || v == kVariantDeepConv) && (dt == DT_BF16 || dt == DT_F16)) return kTile16D;   // three stages
+    if (v == kVariantStream32 && (dt == DT_BF16 || dt == DT_F16)) return kTile16R32;
+    if (v == kVariantStream64 && (dt == DT_BF16 || dt == DT_F16)) return kTile16R64;
     if (v == 1 && dt == DT_F8) return kTileF8S;
     if (v == 1 && dt == DT_F64) return kTileF64L;
     return TileCfg{0, 0, 0};
@@ -141,6 +143,9 @@ void model_for(int dt, int v, double* m) {
     if (v == kVariantDeep || v == kVariantDeepConv) { m[0] = 5.98; m[1] = 1.21; m[2] = 0.581; m[3] = 0.658; m[4] = 0.608; return; }
     if (v == 2) { m[0] = 5.38; m[1] = 1.51; m[2] = 0.583; m[3] = 0.648; m[4] = 0.981; return; }
     if (v == 1 || v == 4) { m[0] = 5.60; m[1] = 1.38; m[2] = 0.603; m[3] = 0.577; m[4] = 0.899; return; }
+    // the streaming tiles: fits over 1024-4096 columns, 1024-8192 k, 1-8 shares a tile
+    if (v == kVariantStream32) { m[0] = 3.70; m[1] = 0.93; m[2] = 0.510; m[3] = 0.725; m[4] = 0.750; return; }
+    if (v == kVariantStream64) { m[0] = 4.75; m[1] = 0.78; m[2] = 0.764; m[3] = 0.670; m[4] = 0.900; return; }
     if (v == 5) { m[0] = 5.99; m[1] = 1.49; m[2] = 0.703; m[3] = 0.570; m[4] = 1.009; return; }
     if (v == 6 || v == 7) { m[0] = 5.28; m[1] = 1.87; m[2] = 0.716; m[3] = 0.551; m[4] = 1.009; return; }
     m[0] = 9.88; m[1] = 2.78; m[2] = 1.351; m[3] = 0.941; m[4] = 1.693;
@@ -595,12 +600,12 @@ static double plan_estimate_compute(const skgemm_plan_s* pl) {
 
 // Plan of tile variant v for the problems of base under options o; nullptr
 // with *st set when the variant cannot run them (SKGEMM_ERR_HIP: out of
-// host memory).  The three-stage small tile holds one workgroup per CU, so a
-// co-residency given in the options counts as 1 for it.
+// host memory).  The three-stage small tile and the streaming tiles hold one
+// workgroup per CU, so a co-residency given in the options counts as 1 for them.
 static skgemm_plan_s* build_variant(const skgemm_plan_s* base, int v, const skgemm_options_t& o, int G,
                                     const int64_t* M, const int64_t* N, const int64_t* K, skgemm_status_t* st) {
     skgemm_options_t ov = o;
-    if ((v == kVariantDeep || v == kVariantDeepConv) && ov.occupancy) ov.occupancy = 1;
+    if ((v == kVariantDeep || v == kVariantDeepConv || is_stream_variant(v)) && ov.occupancy) ov.occupancy = 1;
     const TileCfg tc_ = tile_for(base->dtype, v);
     skgemm_plan_s* pl = new (std::nothrow) skgemm_plan_s(*base);
     if (!pl) {
@@ -636,6 +641,33 @@ static skgemm_plan_s* build_variant(const skgemm_plan_s* base, int v, const skge
     return pl;
 }
 
+// The streaming tile an automatic plan of a single GEMM with both operands
+// K-contiguous takes, or -1.  At most 32 rows (measured over 1 to 32 rows, 1024
+// to 16384 columns and 1024 to 8192 k, odd sizes among them: 1.2-1.7x the best
+// of the other tiles up to one tile per CU, 0.98-1.27x above): always, but for
+// a short second wave of short tiles (13x10715x1152, 335 tiles of 5 slabs: 16.1
+// us against 12.8).  33 to 64 rows: where its tiles fit the CUs in one wave and
+// the rows of both operands start on 128-byte lines (1.0-1.32x); with more
+// tiles, or every run of a slab across a line more, its half of A a slab costs
+// more than the longer runs gain (64x11000x5000 40.7 us on the 64x256 tile, 50.2
+// here).
+static int stream_variant(const skgemm_plan_s* base, const skgemm_options_t& o, const int64_t* M, const int64_t* N,
+                          const int64_t* K) {
+    if (base->G || base->conv || base->batch != 1 || !base->akc || !base->bkc || o.policy != SKGEMM_POLICY_AUTO ||
+        o.force_g || (o.tile_waves && o.tile_waves != 4) || o.tile_m || o.tile_n || o.tile_k)
+        return -1;
+    const int64_t rows = base->swapped ? N[0] : M[0], cols = base->swapped ? M[0] : N[0];
+    int v = -1;
+    if (rows <= kTile16R32.bm) v = kVariantStream32;
+    else if (rows <= kTile16R64.bm && (K[0] * elem_bytes(base->ta)) % 128 == 0) v = kVariantStream64;
+    if (v < 0 || !kernel_exists(base->dtype, true, true, v)) return -1;
+    int cus = o.num_cus, occ = 1;
+    if (!cus && device_capacity(base->dtype, true, true, v, &cus, &occ) != SKGEMM_OK) return -1;
+    const int64_t t = cdiv(cols, kTile16R32.bn), rem = t % cus;
+    if (t > cus && (v == kVariantStream64 || (cdiv(K[0], kTile16R32.bk) < 8 && 5 * rem < 3 * cus && rem))) return -1;
+    return v;
+}
+
 // Builds the plan for every admissible tile variant (the one the options
 // name, else all that exist) and keeps the one with the smallest modelled
 // runtime (the default tile on ties); the small 16-bit tile competes on its
@@ -643,10 +675,12 @@ static skgemm_plan_s* build_variant(const skgemm_plan_s* base, int v, const skge
 static skgemm_status_t plan_variants(skgemm_plan_s* base, const skgemm_options_t& o, int G, const int64_t* M,
                                      const int64_t* N, const int64_t* K, skgemm_plan_s** out) {
     const bool named = o.tile_m || o.tile_n || o.tile_k;
+    const int stream = stream_variant(base, o, M, N, K);
     skgemm_plan_s* cand[kVariants] = {};
     skgemm_status_t last = SKGEMM_ERR_UNSUPPORTED;
     for (int v = 0; v < kVariants; ++v) {
         if (v == kVariantDeep || v == kVariantDeepConv) continue;   // substituted below, not candidates
+        if (!named && (stream >= 0 ? v != stream : is_stream_variant(v))) continue;
         if (is_conv_variant(v) != base->conv) continue;     // the convolution kernels are variants 3, 4 and 7
         // the skinny tile only where every launched problem has at most its
         // 64 rows (unless the options name it)
@@ -842,7 +876,8 @@ static void plan_packing(skgemm_plan_s* pl, int32_t relayout) {
         const double gain = kc ? kPackKcR * mb * panels - kPackKcMb * mb : kPackMnR * mb * panels - kPackMnMb * mb;
         // relayout masks name the caller's A and B; x is the launched operand
         const int caller = pl->swapped ? 1 - x : x;
-        const bool wanted = relayout == 0 ? gain > kPackMarginUs : relayout > 0 && ((relayout >> caller) & 1);
+        // (the rule was not measured on the streaming tiles, which read B once)
+        const bool wanted = relayout == 0 ? gain > kPackMarginUs && !is_stream_variant(pl->variant) : relayout > 0 && ((relayout >> caller) & 1);
         pl->pack[x] = lines > 0 && cols > 0 && (cols * eb) % 128 != 0 && bytes <= kPackMaxBytes &&
                       pl->pack_ld[x] <= kMaxDim && wanted;
         if (pl->pack[x]) {
@@ -1018,6 +1053,8 @@ static skgemm_status_t check_problem(const skgemm_plan_s* pl, int64_t M, int64_t
     e->ldc = ldc;
     // Loads use 32-bit offsets within one tile's slab of each operand.
     const int64_t lim = (int64_t(1) << 31) - 1;
+    // (the last row of a K-contiguous slab ends at most one leading dimension
+    // or, where that is shorter than a slab's rows, a few KiB past its start)
     const int64_t span_a = pl->akc ? int64_t(pl->BM) * e->lda * eb + 128 : int64_t(pl->BK) * e->lda * eb + 512;
     const int64_t span_b = pl->bkc ? int64_t(pl->BN) * e->ldb * eb + 128 : int64_t(pl->BK) * e->ldb * eb + 512;
     if (span_a > lim || span_b > lim) return SKGEMM_ERR_UNSUPPORTED;

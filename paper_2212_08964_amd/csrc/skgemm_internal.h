@@ -36,6 +36,8 @@ constexpr TileCfg kTileF8 = {256, 256, 128, 2};
 constexpr TileCfg kTileF8S = {128, 128, 128, 2};   // fp8, small-tile variant
 constexpr TileCfg kTileF64 = {64, 64, 16, 2};
 constexpr TileCfg kTileF64L = {128, 128, 16, 2};   // fp64, large-tile variant
+constexpr TileCfg kTile16R32 = {32, 32, 256, 4};  // bf16 and f16, streaming tile for M <= 32
+constexpr TileCfg kTile16R64 = {64, 32, 256, 3};  // bf16 and f16, streaming tile for M <= 64
 constexpr TileCfg kTile16D = {128, 128, 64, 3};   // bf16 and f16, small tile on three LDS stages
 
 // One problem of a grouped launch (device table entry, 128 bytes).  Shapes are
@@ -115,9 +117,13 @@ struct KArgs {
 // one workgroup per CU; the planner substitutes it for variants 1 and 2
 // where the grid fits one workgroup per CU, never as a candidate of its own.
 // 9: the same with the convolution gather, substituted for variant 4.
-constexpr int kVariants = 10;
+// 10 and 11: the streaming tiles of 32 and 64 rows (both operands K-contiguous).
+constexpr int kVariants = 12;
 constexpr int kVariantDeep = 8;
 constexpr int kVariantDeepConv = 9;
+constexpr int kVariantStream32 = 10;
+constexpr int kVariantStream64 = 11;
+constexpr bool is_stream_variant(int v) { return v == kVariantStream32 || v == kVariantStream64; }
 constexpr bool is_conv_variant(int v) { return v == 3 || v == 4 || v == 7 || v == 9; }
 
 // Copy `lines` lines of `cols` elements of eb bytes (line i at src + i * ld)

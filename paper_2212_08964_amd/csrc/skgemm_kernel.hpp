@@ -105,6 +105,20 @@ template <> struct Cfg<DT_BF16, 7> : Cfg<DT_BF16, 6> { static constexpr bool CON
 template <> struct Cfg<DT_F16, 9> : Cfg<DT_F16, 8> { static constexpr bool CONV = true; };
 template <> struct Cfg<DT_BF16, 9> : Cfg<DT_BF16, 8> { static constexpr bool CONV = true; };
 
+// Streaming tiles for problems of at most 32 or 64 rows whose B is a
+// K-contiguous weight.  Such a product is bound by the bytes of B from HBM: a
+// plain read of 128 MB in runs of 128 bytes per row (the other tiles' slabs)
+// takes 34 us, in runs of 512 bytes and each XCD a range of rows of its own 26-27.
+// So the tile is 32 columns by 256 k: runs of 512 bytes, and 256 tiles (one
+// per CU, no partial tiles) where a 64x256 tile had 32 and split each six ways.
+// The four waves split the slab's k between them (WK) and add their
+// accumulators up at the end.  16x8192x8192 37.4 -> 28.1 us (4.8 TB/s),
+// 16x4096x4096 17.0 -> 11.1, 64x4096x4096 17.2 -> 13.7.
+template <> struct Cfg<DT_F16, 10> { static constexpr int EB = 2, BM = kTile16R32.bm, BN = kTile16R32.bn, BK = kTile16R32.bk, WM = 1, WN = 1, WK = 4, NS = kTile16R32.ns, WPE = 1; };
+template <> struct Cfg<DT_F16, 11> { static constexpr int EB = 2, BM = kTile16R64.bm, BN = kTile16R64.bn, BK = kTile16R64.bk, WM = 1, WN = 1, WK = 4, NS = kTile16R64.ns, WPE = 1; };
+template <> struct Cfg<DT_BF16, 10> : Cfg<DT_F16, 10> {};
+template <> struct Cfg<DT_BF16, 11> : Cfg<DT_F16, 11> {};
+
 // Optional tile traits: PRIO raises the waves' priority through the MFMA
 // section of each k-slab; WPE overrides the waves per SIMD the register
 // budget is sized for.
