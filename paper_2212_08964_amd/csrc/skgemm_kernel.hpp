@@ -14,9 +14,15 @@
 // tiles, so no lane holds more than 128 FP32 accumulators).  Each k-iteration
 // moves a BM x BK slab of A and a BK x BN slab of B straight from global
 // memory into LDS with buffer loads that write LDS directly (no register
-// staging); two LDS stages alternate so the next slab is in flight while the
+// staging); the LDS stages alternate so the next slabs are in flight while the
 // MFMAs consume the current one.  Each wave accumulates its (BM/WM) x (BN/WN)
-// block with 32x32 MFMA instructions into FP32 registers.
+// block in FP32 registers, with 16x16 MFMA instructions for the 16-bit types
+// and FP64 and 32x32 ones for FP32 and FP8.  What bounds a large 16-bit product
+// is power: on N(0,1) data the matrix cores alone sustain 2096 TFLOP/s with
+// 16x16x32 instructions and 1875 with 32x32x16 (2464 and 2428 on zeros).
+// slab_loop (16-bit and FP8), before it and with it, us: bf16 8192^3 893 -> 803,
+// 2048x2048x8192 on one 128x128 tile per CU 88 -> 76, 3328x2304x3968 75 -> 67;
+// fp8 8192^3 450 -> 408.
 //
 // LDS layouts (no padding; 16-byte chunks XOR-swizzled per row so that the
 // fragment reads of one instruction fall on distinct banks):
@@ -69,8 +75,8 @@ template <int DT, int V> struct Cfg;
 // NS is the number of LDS stages of the MAC-loop pipeline (NS - 1 k-slabs in
 // flight while one is consumed).
 template <> struct Cfg<DT_F32, 0> { static constexpr int EB = 4, BM = kTileF32.bm, BN = kTileF32.bn, BK = kTileF32.bk, WM = 2, WN = 2, NS = kTileF32.ns; };
-template <> struct Cfg<DT_F16, 0> { static constexpr int EB = 2, BM = kTile16.bm, BN = kTile16.bn, BK = kTile16.bk, WM = 2, WN = 4, NS = kTile16.ns; static constexpr bool PRIO = true; };
-template <> struct Cfg<DT_BF16, 0> { static constexpr int EB = 2, BM = kTile16.bm, BN = kTile16.bn, BK = kTile16.bk, WM = 2, WN = 4, NS = kTile16.ns; static constexpr bool PRIO = true; };
+template <> struct Cfg<DT_F16, 0> { static constexpr int EB = 2, BM = kTile16.bm, BN = kTile16.bn, BK = kTile16.bk, WM = 2, WN = 4, NS = kTile16.ns; };
+template <> struct Cfg<DT_BF16, 0> { static constexpr int EB = 2, BM = kTile16.bm, BN = kTile16.bn, BK = kTile16.bk, WM = 2, WN = 4, NS = kTile16.ns; };
 template <> struct Cfg<DT_F8, 0> { static constexpr int EB = 1, BM = kTileF8.bm, BN = kTileF8.bn, BK = kTileF8.bk, WM = 2, WN = 4, NS = kTileF8.ns; };
 template <> struct Cfg<DT_F8, 1> { static constexpr int EB = 1, BM = kTileF8S.bm, BN = kTileF8S.bn, BK = kTileF8S.bk, WM = 2, WN = 2, NS = kTileF8S.ns; };
 template <> struct Cfg<DT_F64, 0> { static constexpr int EB = 8, BM = kTileF64.bm, BN = kTileF64.bn, BK = kTileF64.bk, WM = 2, WN = 2, NS = kTileF64.ns; };
@@ -119,11 +125,8 @@ template <> struct Cfg<DT_F16, 11> { static constexpr int EB = 2, BM = kTile16R6
 template <> struct Cfg<DT_BF16, 10> : Cfg<DT_F16, 10> {};
 template <> struct Cfg<DT_BF16, 11> : Cfg<DT_F16, 11> {};
 
-// Optional tile traits: PRIO raises the waves' priority through the MFMA
-// section of each k-slab; WPE overrides the waves per SIMD the register
-// budget is sized for.
-template <class C, class = void> struct PrioOf { static constexpr bool value = false; };
-template <class C> struct PrioOf<C, std::void_t<decltype(C::PRIO)>> { static constexpr bool value = C::PRIO; };
+// Optional tile traits: WPE overrides the waves per SIMD the register budget
+// is sized for.
 template <class C, class = void> struct ConvOf { static constexpr bool value = false; };
 template <class C> struct ConvOf<C, std::void_t<decltype(C::CONV)>> { static constexpr bool value = C::CONV; };
 
@@ -247,7 +250,14 @@ struct Slab {
                   "MN-contiguous slab rows must be 256, 512 or 1024 bytes");
     static_assert(BLOCKS % NW == 0, "slab must split evenly over the waves");
 
-    uint32_t voff[PER_WAVE];     // byte offset of the lane's chunk from the slab origin
+    // Rows between a lane's consecutive chunks.  Where the swizzle repeats after
+    // that many rows, the chunks lie a uniform distance apart and one offset
+    // per lane serves them all (a vector addition each, behind the MFMAs, for
+    // registers the accumulators need); else every chunk has its own.
+    static constexpr int ROWS_STEP = NW * 1024 / ROWB;
+    static constexpr bool UNIFORM = ROWS_STEP % 16 == 0 || (EB != 2 && !KC && ROWS_STEP % (EB == 4 ? 8 : 4) == 0);
+    uint32_t voff[UNIFORM ? 1 : PER_WAVE];     // byte offsets of the lane's chunks from the slab origin
+    uint32_t vstep;              // UNIFORM: bytes between them
     const unsigned char* base;   // operand address of (outer o0, k of the first iteration)
     int64_t bytes;               // operand bytes from base to its end
     int64_t step;                // bytes between consecutive k-iterations
@@ -272,7 +282,15 @@ struct Slab {
         ahead = reinterpret_cast<uint64_t>(base);
         left = bytes;
 #pragma unroll
-        for (int j = 0; j < PER_WAVE; ++j) voff[j] = chunk_off(j, tid);
+        for (int j = 0; j < (UNIFORM ? 1 : PER_WAVE); ++j) voff[j] = chunk_off(j, tid);
+        vstep = uint32_t(ROWS_STEP) * ldb;
+    }
+
+    // Offset of the lane's chunk j of a slab wholly inside the inner edge.
+    template <int J>
+    __device__ __forceinline__ uint32_t off() const {
+        if constexpr (UNIFORM) return voff[0] + uint32_t(J) * vstep;
+        else return voff[J];
     }
 
     __device__ __forceinline__ uint32_t chunk_off(int j, int tid) const {
@@ -323,35 +341,28 @@ struct Slab {
     // element-by-element path.
     static __device__ __forceinline__ bool whole(uint32_t off, uint32_t nr) { return off + 16u <= nr; }
 
-    // Descriptor of the next slab, whose first k is k0, with the lane's chunk
-    // offsets in voff.  EDGE = false: the slab is
-    // wholly inside the inner edge and voff is as init left it; a checked slab
-    // recomputes voff with the chunks to skip out of range (once checked, a
-    // segment's remaining slabs are all checked).
-    template <bool EDGE>
-    __device__ __forceinline__ i32x4 prepare(int k0, int K, int o0, int dout, int tid) {
-        const i32x4 d = next_desc();
-        if constexpr (EDGE) {
-            tid = opaque(tid);
-            const bool tail = KC ? (k0 + BK > K) : (o0 + R > dout);
-            const int lim = KC ? (K - k0) : (dout - o0);
-#pragma unroll
-            for (int j = 0; j < PER_WAVE; ++j) {
-                const int kp = keep(j, tail, lim, tid);
-                voff[j] = chunk_off(j, tid);
-                if (kp == 0 || (kp < VE && !whole(voff[j], uint32_t(d[2])))) voff[j] = 0x80000000u;
-            }
-        }
-        return d;
-    }
+    // Descriptor of the next slab (its first k is k0).
+    __device__ __forceinline__ i32x4 prepare(int, int) { return next_desc(); }
 
-    // Issue the direct-to-LDS loads of one slab into the stage at LDS address `lds`.
+    // Issue the direct-to-LDS loads of the next slab, whose first k is k0, into
+    // the stage at LDS address `lds`.  EDGE = false: the caller knows the slab is
+    // wholly inside the inner edge (no per-chunk checks).
     template <bool EDGE>
     __device__ __forceinline__ void issue(int k0, int K, int o0, int dout, uint32_t lds, int tid) {
-        const i32x4 d = prepare<EDGE>(k0, K, o0, dout, tid);
+        const i32x4 d = next_desc();
+        if constexpr (EDGE) tid = opaque(tid);
+        const bool tail = EDGE && (KC ? (k0 + BK > K) : (o0 + R > dout));
+        const int lim = KC ? (K - k0) : (dout - o0);
         lds += uint32_t(uni(tid >> 6)) * 1024;
 #pragma unroll
-        for (int j = 0; j < PER_WAVE; ++j) dma16(d, voff[j], lds + j * NW * 1024);
+        for (int j = 0; j < PER_WAVE; ++j) {
+            uint32_t at = UNIFORM ? voff[0] + uint32_t(j) * vstep : voff[UNIFORM ? 0 : j];
+            if constexpr (EDGE) {
+                const int kp = keep(j, tail, lim, tid);
+                if (kp == 0 || (kp < VE && !whole(at, uint32_t(d[2])))) at = 0x80000000u;
+            }
+            dma16(d, at, lds + j * NW * 1024);
+        }
     }
 
     // After the stage's loads have landed: clear the bytes past the edge of
@@ -464,8 +475,7 @@ struct ConvSlab {
     }
 
     // Slab of reduction indices [k0, k0 + BK): filter tap k0 / C, channels k0 mod C on.
-    template <bool EDGE>
-    __device__ __forceinline__ i32x4 prepare(int k0, int, int, int, int tid) {
+    __device__ __forceinline__ i32x4 prepare(int k0, int tid) {
         const int rs = k0 / C, c0 = k0 - rs * C;
         const int r = rs / S, s = rs - r * S;
 #pragma unroll
@@ -478,10 +488,12 @@ struct ConvSlab {
         return i32x4{uni(int(uint32_t(reinterpret_cast<uint64_t>(x)))),
                      uni(int(uint32_t(reinterpret_cast<uint64_t>(x) >> 32) & 0xffffu)), int(bytes), kBufferFlags};
     }
+    template <int J>
+    __device__ __forceinline__ uint32_t off() const { return voff[J]; }
 
     template <bool EDGE>
-    __device__ __forceinline__ void issue(int k0, int K, int o0, int dout, uint32_t lds, int tid) {
-        const i32x4 d = prepare<EDGE>(k0, K, o0, dout, tid);
+    __device__ __forceinline__ void issue(int k0, int, int, int, uint32_t lds, int tid) {
+        const i32x4 d = prepare(k0, tid);
         lds += uint32_t(uni(tid >> 6)) * 1024;
 #pragma unroll
         for (int j = 0; j < PER_WAVE; ++j) dma16(d, voff[j], lds + j * NW * 1024);
@@ -686,6 +698,7 @@ struct Gemm {
     // or four 16x16 ones (16-bit types and FP64; q = 2 * row half + column
     // half), so bands and blocks cover the same rows and columns for every type.
     static constexpr bool kHalf = DT == DT_BF16 || DT == DT_F16;
+    static constexpr bool kSeam = kHalf || DT == DT_F8;      // MAC loop: slab_loop (else step)
     struct Acc32 { f32x16 v[FM][FN]; };
     struct Acc16 { f32x4 v[FM][FN][4]; };
     struct Acc64 { f64x4 v[FM][FN][4]; };
@@ -774,7 +787,7 @@ struct Gemm {
     static __device__ __forceinline__ void compute(const unsigned char* As, const unsigned char* Bs,
                                                    Acc& acc, int wm, int wn, int lane) {
         const int g = lane >> 5, l32 = lane & 31;
-        static_assert(!kHalf, "16-bit types run slab_loop");
+        static_assert(!kSeam, "16-bit types and FP8 run slab_loop");
         if constexpr (DT == DT_F64) {
             // v_mfma_f64_16x16x4f64: lane l holds A[row l%16][k l/16] and
             // B[k l/16][col l%16] of the k4 step; each 32x32 block is four
@@ -801,7 +814,7 @@ struct Gemm {
                             acc.v[i][j][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[i][q >> 1], bf[j][q & 1],
                                                                                  acc.v[i][j][q], 0, 0, 0);
             }
-        } else if constexpr (DT == DT_F32) {
+        } else {
             // Lane group g handles k = 8c + 4g + u of step (c, u).
 #pragma unroll
             for (int c = 0; c < BK / 8; ++c) {
@@ -835,37 +848,6 @@ struct Gemm {
 #pragma unroll
                         for (int j = 0; j < FN; ++j)
                             acc.v[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][u], bf[j][u], acc.v[i][j], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-            static_assert(AKC && BKC, "FP8 operands must be K-contiguous");
-            // Lane group g handles k = 64s + 32g .. +31 of step s (two chunks).
-            // Not unrolled, and B fragments for the step, then one A
-            // fragment at a time: the fewest registers in flight.  Any spill
-            // would make the kernel use scratch memory, and a kernel with
-            // scratch pays a fixed cost of about 20 us per launch on this GPU.
-#pragma unroll 1
-            for (int s = 0; s < BK / 64; ++s) {
-                i32x8 bf[FN];
-#pragma unroll
-                for (int j = 0; j < FN; ++j) {
-                    const int row = wn * WTN + j * 32 + l32;
-                    const u32x4 lo = lds_row_chunk<EB, SB::ROWB>(Bs, row, 4 * s + 2 * g);
-                    const u32x4 hi = lds_row_chunk<EB, SB::ROWB>(Bs, row, 4 * s + 2 * g + 1);
-                    bf[j] = i32x8{int(lo.x), int(lo.y), int(lo.z), int(lo.w), int(hi.x), int(hi.y), int(hi.z), int(hi.w)};
-                }
-#pragma unroll
-                for (int i = 0; i < FM; ++i) {
-                    const int row = wm * WTM + i * 32 + l32;
-                    const u32x4 lo = lds_row_chunk<EB, SA::ROWB>(As, row, 4 * s + 2 * g);
-                    const u32x4 hi = lds_row_chunk<EB, SA::ROWB>(As, row, 4 * s + 2 * g + 1);
-                    const i32x8 af = i32x8{int(lo.x), int(lo.y), int(lo.z), int(lo.w), int(hi.x), int(hi.y),
-                                           int(hi.z), int(hi.w)};
-#pragma unroll
-                    for (int j = 0; j < FN; ++j)
-                        acc.v[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                            af, bf[j], acc.v[i][j], 0, 0, 0, 127, 0, 127);
-                }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -974,10 +956,10 @@ struct Gemm {
         (prologue_one<J>(a, sa, sb, kbeg, kend, kedge, m0, n0, st, tid), ...);
     }
 
-    // ---- 16-bit types: fragments carried across the slab seam
+    // ---- 16-bit types and FP8: fragments carried across the slab seam
     //
-    // A wave's block is FA x FB blocks of 16x16.  A slab is two k32 steps.  In
-    // slot i of a step the wave runs the MFMAs of A fragment i with every B
+    // A wave's block is FA x FB blocks of 16x16 (FP8: 32x32).  A slab is two steps
+    // of k32 (k64).  In slot i of a step the wave runs the MFMAs of A fragment i with every B
     // fragment, and then reads fragment i of the next step into the registers
     // just freed; the B fragments, in use throughout a step, have two buffers.
     // The second step of a slab runs behind the seam: once its fragments are
@@ -986,25 +968,34 @@ struct Gemm {
     // refilled, while the matrix cores work on that step.  The refill's loads
     // are spread one by one between the MFMAs: issued in one burst ahead of
     // them, the memory pipeline's queue kept the waves from their MFMAs.
-    static constexpr int FA = WTM / 16, FB = WTN / 16;
+    static constexpr int FA = kHalf ? WTM / 16 : FM, FB = kHalf ? WTN / 16 : FN;
     static constexpr bool kStream = kHalf && (WK > 1 || V == 5 || V == 6 || V == 7);
     // Slot in which the last A fragment of the second step is read ahead, into
-    // a spare register set, so that the seam does not wait for it.
-    static constexpr int SPARE = FA > 4 ? FA - 3 : FA - 2;
+    // a spare register set, so that the seam does not wait for it (the FP8
+    // 256x256 tile has no registers to spare).
+    static constexpr int SPARE = DT == DT_F8 && BM * BN >= 256 * 256 ? -1 : FA > 4 ? FA - 3 : FA > 2 ? FA - 2 : 0;
 
-    // Slots of the second step over which the refill's loads are issued.
-    static constexpr int SPREAD = FA > 4 ? 8 : 1;
+    using Frag = typename Pick<DT == DT_F8, i32x8, u32x4>::type;
+    struct Frags { Frag a[FA], b[2][FB], spare; };
 
-    struct Frags { u32x4 a[FA], b[2][FB], spare; };
+    // FP8: 32 consecutive k of row `row` (lane group g's half of the step's 64).
+    template <int ROWB>
+    static __device__ __forceinline__ i32x8 read_f8(const unsigned char* lds, int row, int s, int g) {
+        const u32x4 lo = lds_row_chunk<EB, ROWB>(lds, row, 4 * s + 2 * g);
+        const u32x4 hi = lds_row_chunk<EB, ROWB>(lds, row, 4 * s + 2 * g + 1);
+        return i32x8{int(lo.x), int(lo.y), int(lo.z), int(lo.w), int(hi.x), int(hi.y), int(hi.z), int(hi.w)};
+    }
 
     template <int I>
-    static __device__ __forceinline__ u32x4 read_a(int s, const unsigned char* As, int wm, int lane) {
-        if constexpr (AKC) return lds_row_chunk<EB, SA::ROWB>(As, wm * WTM + I * 16 + (lane & 15), 4 * s + (lane >> 4));
+    static __device__ __forceinline__ Frag read_a(int s, const unsigned char* As, int wm, int lane) {
+        if constexpr (DT == DT_F8) return read_f8<SA::ROWB>(As, wm * WTM + I * 32 + (lane & 31), s, lane >> 5);
+        else if constexpr (AKC) return lds_row_chunk<EB, SA::ROWB>(As, wm * WTM + I * 16 + (lane & 15), 4 * s + (lane >> 4));
         else return lds_tr16<SA::ROWB, I>(As, s, wm * WTM, lane);
     }
     template <int J>
-    static __device__ __forceinline__ u32x4 read_b(int s, const unsigned char* Bs, int wn, int lane) {
-        if constexpr (BKC) return lds_row_chunk<EB, SB::ROWB>(Bs, wn * WTN + J * 16 + (lane & 15), 4 * s + (lane >> 4));
+    static __device__ __forceinline__ Frag read_b(int s, const unsigned char* Bs, int wn, int lane) {
+        if constexpr (DT == DT_F8) return read_f8<SB::ROWB>(Bs, wn * WTN + J * 32 + (lane & 31), s, lane >> 5);
+        else if constexpr (BKC) return lds_row_chunk<EB, SB::ROWB>(Bs, wn * WTN + J * 16 + (lane & 15), 4 * s + (lane >> 4));
         else return lds_tr16<SB::ROWB, J>(Bs, s, wn * WTN, lane);
     }
     template <int J0, int J1>
@@ -1029,8 +1020,8 @@ struct Gemm {
 
     template <int J>
     static __device__ __forceinline__ void refill_one(const Refill& rf, const SA& sa, const SB& sb) {
-        if constexpr (J < SB::PER_WAVE) dma16_at<SA::BYTES + J * NW * 1024>(rf.db, sb.voff[J], rf.lds);
-        else dma16_at<(J - SB::PER_WAVE) * NW * 1024>(rf.da, sa.voff[J - SB::PER_WAVE], rf.lds);
+        if constexpr (J < SB::PER_WAVE) dma16_at<SA::BYTES + J * NW * 1024>(rf.db, sb.template off<J>(), rf.lds);
+        else dma16_at<(J - SB::PER_WAVE) * NW * 1024>(rf.da, sa.template off<J - SB::PER_WAVE>(), rf.lds);
     }
     template <int J0, int J1>
     static __device__ __forceinline__ void refill_range(const Refill& rf, const SA& sa, const SB& sb) {
@@ -1046,15 +1037,24 @@ struct Gemm {
     static __device__ __forceinline__ void slot(Frags& f, const unsigned char* As, const unsigned char* Bs, Acc& acc,
                                                 const Refill& rf, const SA& sa, const SB& sb, int wm, int wn,
                                                 int lane) {
-        if constexpr (REFILL && I < SPREAD) refill_range<I * LOADS / SPREAD, (I + 1) * LOADS / SPREAD>(rf, sa, sb);
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (REFILL) {
+            refill_range<I * LOADS / FA, (I + 1) * LOADS / FA>(rf, sa, sb);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int j = 0; j < FB; ++j) {
-            f32x4& c = acc.v[I / 2][j / 2][2 * (I & 1) + (j & 1)];
-            c = mfma16<DT>(f.a[I], f.b[S][j], c);
+            if constexpr (DT == DT_F8) {
+                acc.v[I][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f.a[I], f.b[S][j], acc.v[I][j], 0, 0, 0,
+                                                                            127, 0, 127);
+            } else {
+                f32x4& c = acc.v[I / 2][j / 2][2 * (I & 1) + (j & 1)];
+                c = mfma16<DT>(f.a[I], f.b[S][j], c);
+            }
         }
+        // (the fragments read next go into the registers of those just used)
+        if constexpr (DT == DT_F8) __builtin_amdgcn_sched_barrier(0);
         if constexpr (S == 0 && I == SPARE) f.spare = read_a<FA - 1>(1, As, wm, lane);
-        if constexpr (S == 0 && I == FA - 1) f.a[I] = f.spare;
+        if constexpr (SPARE >= 0 && S == 0 && I == FA - 1) f.a[I] = f.spare;
         else f.a[I] = read_a<I>(S ^ 1, As, wm, lane);
         // the B fragments in the first half of the step
         constexpr int H = FA / 2;
@@ -1069,64 +1069,86 @@ struct Gemm {
         (slot<I, S, REFILL>(f, As, Bs, acc, rf, sa, sb, wm, wn, lane), ...);
     }
 
-    // Refill of the stage at `lds` with slab `it`.
-    static __device__ __forceinline__ void prep_refill(Refill& rf, const Prob& a, SA& sa, SB& sb, int it, int kbeg,
-                                                       int kedge, int m0, int n0, uint32_t lds, int tid) {
+    // Refill of the stage at `lds` with slab `it`, wholly inside the inner edges.
+    static __device__ __forceinline__ void prep_refill(Refill& rf, SA& sa, SB& sb, int it, uint32_t lds, int tid) {
         rf.lds = lds;
-        if (it >= kedge) {
-            rf.da = sa.template prepare<true>(it * BK, a.K, m0, a.M, tid);
-            rf.db = sb.template prepare<true>(it * BK, a.K, n0, a.N, tid);
-        } else {
-            rf.da = sa.template prepare<false>(it * BK, a.K, m0, a.M, tid);
-            rf.db = sb.template prepare<false>(it * BK, a.K, n0, a.N, tid);
-        }
+        rf.da = sa.prepare(it * BK, tid);
+        rf.db = sb.prepare(it * BK, tid);
     }
 
     // Slabs [kbeg, kend), the first NS - 1 of them in flight, the first
-    // landed: a loop that refills each stage once it is consumed, and one for
-    // the slabs with nothing left to refill (loads past the end, masked out or
+    // landed: a loop that refills each stage once it is consumed, as long as the
+    // refill needs no edge checks, and one for the slabs behind it, which have a
+    // checked refill (in one burst) or none (loads past the end, masked out or
     // through empty descriptors, cost 0.3-0.5 us at the end of a segment; a
     // branch around each, 2-5 %).  The stages lie one after another in LDS and
     // are picked by offset: one copy of each body and one way through it keep the
     // accumulators in place.
     static __device__ __forceinline__ void slab_loop(const Prob& a, SA& sa, SB& sb, int kbeg, int kend, int kedge,
                                                      int m0, int n0, const Stages& st, Acc& acc, int tid) {
-        static_assert(BK == 64 && FA >= 4 && FB >= 2 && WK == 1, "two k32 steps a slab");
+        static_assert(BK * EB == 128 && FA >= 2 && FB >= 2 && WK == 1, "two steps a slab");
         using Slots = std::make_integer_sequence<int, FA>;
         const int lane = tid & 63, w = uni(tid >> 6), wm = (tid >> 6) / WN, wn = (tid >> 6) % WN;
-        const uint32_t dst = lds_addr(st.template at<0>()) + w * 1024;
+        const uint32_t base = lds_addr(st.template at<0>()), dst = base + w * 1024;
         unsigned char* const lds = st.template at<0>();
         Frags f;
         Refill rf;
         read_bs<0, FB>(f, 0, 0, lds + SA::BYTES, wn, lane);
         read_as(f, 0, lds, wm, lane, Slots{});
         if (kbeg + NS - 1 < kend) {
-            prep_refill(rf, a, sa, sb, kbeg + NS - 1, kbeg, kedge, m0, n0, dst + (NS - 1) * STAGE, tid);
-            refill_range<0, LOADS>(rf, sa, sb);
+            issue_b(a, sb, kbeg + NS - 1 >= kedge, kbeg + NS - 1, n0, base + (NS - 1) * STAGE + SA::BYTES, tid);
+            issue_a(a, sa, kbeg + NS - 1 >= kedge, kbeg + NS - 1, m0, base + (NS - 1) * STAGE, tid);
         }
         int cur = 0;                       // byte offset of the stage of slab `it`
         int it = kbeg;
-        for (; it + NS < kend; ++it) {
+        const int plain = min(kend, kedge);
+        for (; it + NS < plain; ++it) {
             half_slab<0, false>(f, lds + cur, lds + cur + SA::BYTES, acc, rf, sa, sb, wm, wn, lane, Slots{});
             const int nxt = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
+            // A wave that has its next slab and is at its MFMAs goes ahead of one that
+            // waits (without it, workgroups sharing a CU drifted apart: the slowest
+            // of 512 at 4427x2519x3013 took 64 us where the mean was 54).
+            __builtin_amdgcn_s_setprio(0);
             wait_vmem_le<LOADS * (NS - 2)>();
-            if (it + 1 >= kedge) fix_slab(a, sa, sb, it + 1, kbeg, m0, n0, lds + nxt, tid);
             step_barrier();
-            prep_refill(rf, a, sa, sb, it + NS, kbeg, kedge, m0, n0, dst + cur, tid);
+            prep_refill(rf, sa, sb, it + NS, dst + cur, tid);
+            __builtin_amdgcn_s_setprio(1);
             half_slab<1, true>(f, lds + nxt, lds + nxt + SA::BYTES, acc, rf, sa, sb, wm, wn, lane, Slots{});
             cur = nxt;
         }
+        __builtin_amdgcn_s_setprio(0);
         for (; it < kend; ++it) {
             half_slab<0, false>(f, lds + cur, lds + cur + SA::BYTES, acc, rf, sa, sb, wm, wn, lane, Slots{});
             const int nxt = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
-            wait_slab(kend - 2 - it);
+            pin(acc);
+            wait_slab(min(NS - 2, kend - 2 - it));
             if (it + 1 >= kedge && it + 1 < kend) fix_slab(a, sa, sb, it + 1, kbeg, m0, n0, lds + nxt, tid);
             step_barrier();
+            if (it + NS < kend) {
+                issue_b(a, sb, true, it + NS, n0, base + cur + SA::BYTES, tid);
+                issue_a(a, sa, true, it + NS, m0, base + cur, tid);
+            }
             // (behind the last slab the fragments read here are never used)
             half_slab<1, false>(f, lds + nxt, lds + nxt + SA::BYTES, acc, rf, sa, sb, wm, wn, lane, Slots{});
             cur = nxt;
         }
         // Every wave has read the last slab before the last barrier.
+    }
+
+    // The accumulators' values are needed here: keeps the compiler from moving
+    // the MFMAs behind the edge fix (with their fragments, in registers it needs).
+    static __device__ __forceinline__ void pin(Acc& acc) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                if constexpr (kHalf) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(acc.v[i][j][q]));
+                } else {
+                    asm volatile("" : "+v"(acc.v[i][j]));
+                }
+            }
     }
 
     static __device__ __forceinline__ void fix_slab(const Prob& a, const SA& sa, const SB& sb, int it, int kbeg, int m0,
@@ -1263,7 +1285,7 @@ struct Gemm {
         }
         step_barrier();
         if constexpr (kStream) {
-        } else if constexpr (kHalf) {
+        } else if constexpr (kSeam) {
             slab_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, tid);
         } else {
             for (int kk = kbeg;; kk += NS)
@@ -1908,8 +1930,8 @@ __global__ void __launch_bounds__((kThreadsOf<DT, V>)) __attribute__((amdgpu_wav
 skgemm_kernel(KArgs a) {
     using G = Gemm<DT, AKC, BKC, V>;
     constexpr int S = G::STAGE;
-    if constexpr (G::kHalf) {
-        // one block: the 16-bit MAC loop picks its stages by offset
+    if constexpr (G::kSeam) {
+        // one block: the MAC loop of these types picks its stages by offset
         __shared__ __attribute__((aligned(1024))) unsigned char st[G::NS * S];
         typename G::Stages sts{st, st + S, st + 2 * S, st + 3 * S, st + 4 * S};
         G::template run<FULL>(a, sts);
