@@ -88,7 +88,7 @@ def test_stream_integer_exact_every_schedule_and_trace(tile):
 
 def test_stream_rule():
     """Automatic plans take the streaming tiles exactly where the rule says:
-    both operands K-contiguous, at most 32 rows (but for a short second wave of
+    both operands K-contiguous, at most 32 rows (but for a short last wave of
     short tiles), or at most 64 with rows on 128-byte lines and at most one tile
     per CU; never for other policies, layouts, types, batches or groups, nor
     where the options ask for another tile or for eight waves."""
@@ -99,10 +99,10 @@ def test_stream_rule():
         return s.Plan(M, N, K, lb=lb, ta=ta, **{**kw, **k}).info()["tile"][:3]
 
     for ta in (s.BF16, s.F16):
-        for M, N, K in [(1, 1, 1), (32, 8192, 8192), (16, 20000, 333)]:
+        for M, N, K in [(1, 1, 1), (32, 8192, 8192)]:
             assert tile(M, N, K, ta=ta) == TILES[0]
         assert tile(33, 8192, 4096, ta=ta) == tile(64, 100, 64, ta=ta) == TILES[1]
-        for M, N, K in [(64, 8193, 4096), (33, 4096, 4100), (65, 4096, 4096), (16, 10000, 1000)]:
+        for M, N, K in [(64, 8193, 4096), (33, 4096, 4100), (65, 4096, 4096), (16, 10000, 1000), (16, 20000, 333)]:
             assert tile(M, N, K, ta=ta) not in TILES
     assert tile(8192, 16, 4096, la=s.ROW_MAJOR, lc=s.COL_MAJOR) == TILES[0]      # 16 rows as launched
     for k in [dict(lb=s.ROW_MAJOR), dict(la=s.COL_MAJOR), dict(policy="dp"), dict(policy="sk"), dict(ta=s.F32),
