@@ -59,6 +59,7 @@ const void* kernel_table(bool akc, bool bkc, int v) {
             case 9: return kc_only<DT, 9, FULL>(akc, bkc);     // the same, convolution
             case 10: return kc_only<DT, 10, FULL>(akc, bkc);   // streaming tiles
             case 11: return kc_only<DT, 11, FULL>(akc, bkc);
+            case 12: return any_layout<DT, 12, FULL>(akc, bkc);  // quarter-size tile
             default: return nullptr;
         }
     } else if constexpr (DT == DT_F8) {
@@ -75,7 +76,11 @@ const void* kernel_table(bool akc, bool bkc, int v) {
         }
     } else {
         static_assert(DT == DT_F32, "input types");
-        return v == 0 ? any_layout<DT, 0, FULL>(akc, bkc) : nullptr;
+        switch (v) {
+            case 0: return any_layout<DT, 0, FULL>(akc, bkc);
+            case 1: return any_layout<DT, 1, FULL>(akc, bkc);
+            default: return nullptr;
+        }
     }
 }
 

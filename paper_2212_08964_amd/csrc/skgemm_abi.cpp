@@ -115,6 +115,8 @@ TileCfg tile_for(int dt, int v) {
     if ((v == kVariantDeep || v == kVariantDeepConv) && (dt == DT_BF16 || dt == DT_F16)) return kTile16D;   // three stages
     if (v == kVariantStream32 && (dt == DT_BF16 || dt == DT_F16)) return kTile16R32;
     if (v == kVariantStream64 && (dt == DT_BF16 || dt == DT_F16)) return kTile16R64;
+    if (v == kVariantQuarter && (dt == DT_BF16 || dt == DT_F16)) return kTile16Q;
+    if (v == 1 && dt == DT_F32) return kTileF32S;
     if (v == 1 && dt == DT_F8) return kTileF8S;
     if (v == 1 && dt == DT_F64) return kTileF64L;
     return TileCfg{0, 0, 0};
@@ -136,6 +138,9 @@ void model_for(int dt, int v, double* m) {
     // twice the MFMA rate.
     if (dt == DT_F64 && v == 1) { m[0] = 7.98; m[1] = 1.22; m[2] = 2.04; m[3] = 1.13; m[4] = 3.84; return; }
     if (dt == DT_F64) { m[0] = 5.00; m[1] = 1.23; m[2] = 0.713; m[3] = 1.13; m[4] = 2.09; return; }
+    // the quarter-size tiles: fits over 1-256 (fp32: 1-1024) workgroups, 1-8 shares a tile
+    if (v == kVariantQuarter) { m[0] = 4.73; m[1] = 1.37; m[2] = 0.243; m[3] = 0.525; m[4] = 0.505; return; }
+    if (dt == DT_F32 && v == 1) { m[0] = 4.55; m[1] = 1.37; m[2] = 0.762; m[3] = 0.585; m[4] = 2.450; return; }
     if (dt == DT_F32) { m[0] = 6.20; m[1] = 1.25; m[2] = 2.07; m[3] = 0.569; m[4] = 3.99; return; }
     // the convolution variants take the constants of the GEMM tile of their shape
     // the three-stage small tile: calibrate.py's grid mode with e from one
@@ -586,7 +591,14 @@ static double plan_estimate_compute(const skgemm_plan_s* pl) {
     const double* m = pl->model;
     const double a = m[0], b = m[1], c = m[2], d = m[3], e = m[4];
     // per-iteration time with `active` of the p workgroup slots busy
-    auto c_at = [&](int64_t active) { return c + (e - c) * std::min(1.0, double(active) / pl->p); };
+    // (the quarter-size tiles, whose workgroups share a CU from the CU count on, by
+    // the workgroups on the busiest CU, as the split rule does)
+    const int64_t cus = std::max<int64_t>(1, pl->p / std::max(1, pl->occ));
+    auto c_at = [&](int64_t active) {
+        if (is_quarter_variant(pl->dtype, pl->variant))
+            return pl->occ <= 1 ? c : c + (e - c) * double(std::min<int64_t>(pl->occ, cdiv(active, cus)) - 1) / (pl->occ - 1);
+        return c + (e - c) * std::min(1.0, double(active) / pl->p);
+    };
     if (pl->g_sk == 0) {
         const int64_t full = pl->t / pl->p, rem = pl->t % pl->p;
         return double(full) * (a + e * ipt) + (rem ? a + c_at(rem) * ipt : 0.0);
@@ -645,8 +657,8 @@ static skgemm_plan_s* build_variant(const skgemm_plan_s* base, int v, const skge
 // K-contiguous takes, or -1.  At most 32 rows (measured over 1 to 32 rows, 1024
 // to 16384 columns and 1024 to 8192 k, odd sizes among them: 1.2-1.7x the best
 // of the other tiles up to one tile per CU, 0.98-1.27x above): always, but for
-// a short second wave of short tiles (13x10715x1152, 335 tiles of 5 slabs: 16.1
-// us against 12.8).  33 to 64 rows: where its tiles fit the CUs in one wave and
+// a short last wave of short tiles (13x10715x1152, 335 tiles of 5 slabs: 16.1
+// us against 12.8; 16x20000x333, 625 of 2: 20.3 against 10.2).  33 to 64 rows: where its tiles fit the CUs in one wave and
 // the rows of both operands start on 128-byte lines (1.0-1.32x); with more
 // tiles, or every run of a slab across a line more, its half of A a slab costs
 // more than the longer runs gain (64x11000x5000 40.7 us on the 64x256 tile, 50.2
@@ -668,6 +680,30 @@ static int stream_variant(const skgemm_plan_s* base, const skgemm_options_t& o, 
     return v;
 }
 
+// A quarter-size tile is taken where the model has it this much faster than the
+// others: it moves twice the operand bytes through L2, which the model's
+// constants, fitted on problems that stay in cache, do not see (1024x1024x4096,
+// modelled 5 % faster, measured 20.9 us against 20.0).
+constexpr double kQuarterGain = 0.90;
+
+// The quarter-size tiles compete for automatic plans of one GEMM or batch; the
+// 16-bit one, which has the skinny and tall tiles beside it, with more than 64
+// rows and columns, and up to two tiles per CU (more: 1536x1536x512, 576 tiles,
+// 10.3 us against 9.8 on the 128x128 tile; 2048x2048x512, 1024 tiles, 14.3
+// against 11.0), with more than one only up to 16 slabs a tile (608x2876x1345,
+// 450 tiles of 22 slabs, 17.6 us against 15.5; 1024x1728x896, 432 of 14, 10.5
+// against 12.6).
+static bool quarter_fits(const skgemm_plan_s* base, int v, const skgemm_options_t& o, const int64_t* M,
+                         const int64_t* N, const int64_t* K) {
+    if (base->G || o.policy != SKGEMM_POLICY_AUTO || o.force_g || o.tile_waves) return false;
+    if (base->dtype == DT_F32) return true;
+    if (M[0] <= kTile16K.bm || N[0] <= kTile16T.bn) return false;
+    int cus = o.num_cus, occ = 1;
+    if (!cus && device_capacity(base->dtype, base->akc, base->bkc, v, &cus, &occ) != SKGEMM_OK) return false;
+    const int64_t t = cdiv(M[0], kTile16Q.bm) * cdiv(N[0], kTile16Q.bn) * base->batch;
+    return t <= cus || (t <= 2 * int64_t(cus) && cdiv(K[0], kTile16Q.bk) <= 16);
+}
+
 // Builds the plan for every admissible tile variant (the one the options
 // name, else all that exist) and keeps the one with the smallest modelled
 // runtime (the default tile on ties); the small 16-bit tile competes on its
@@ -680,7 +716,11 @@ static skgemm_status_t plan_variants(skgemm_plan_s* base, const skgemm_options_t
     skgemm_status_t last = SKGEMM_ERR_UNSUPPORTED;
     for (int v = 0; v < kVariants; ++v) {
         if (v == kVariantDeep || v == kVariantDeepConv) continue;   // substituted below, not candidates
+        // the streaming and quarter-size tiles by their rules, or named in full
         if (!named && (stream >= 0 ? v != stream : is_stream_variant(v))) continue;
+        if (!named && is_quarter_variant(base->dtype, v) && !quarter_fits(base, v, o, M, N, K)) continue;
+        if (named && !(o.tile_m && o.tile_n && o.tile_k) && (is_stream_variant(v) || is_quarter_variant(base->dtype, v)))
+            continue;
         if (is_conv_variant(v) != base->conv) continue;     // the convolution kernels are variants 3, 4 and 7
         // the skinny tile only where every launched problem has at most its
         // 64 rows (unless the options name it)
@@ -704,6 +744,38 @@ static skgemm_status_t plan_variants(skgemm_plan_s* base, const skgemm_options_t
         if (o.tile_waves && kernel_threads(base->dtype, v) != 64 * o.tile_waves) continue;
         skgemm_status_t st = SKGEMM_OK;
         skgemm_plan_s* pl = build_variant(base, v, o, G, M, N, K, &st);
+        // An automatic plan of the quarter-size 16-bit tile splits its tiles over
+        // at most two workgroups per CU (three: 960x832x3456, 195 tiles on 585, 18.1 us
+        // against 17.4 on the 128x128 tile; 24 of 484x103x1113, 384 on 768, 19.5
+        // against 18.2),
+        // and over more than one only up to 64 slabs a tile (2145x158x5418, 102 on
+        // 510, 85 slabs: 21.8 against 21.1; 1920x320x2944, 46: 13.9 against 16.4).
+        if (pl && v == kVariantQuarter && !named && pl->g_sk > 0 && pl->occ > 0) {
+            const int64_t cus = pl->p / pl->occ;
+            skgemm_options_t oq = o;
+            if (pl->grid > 2 * cus) {
+                const int64_t g = 2 * cus / pl->t * pl->t;
+                oq.policy = g > pl->t ? SKGEMM_POLICY_SK : SKGEMM_POLICY_DP;
+                if (g > pl->t) oq.force_g = int32_t(g);
+                delete pl;
+                pl = build_variant(base, v, oq, G, M, N, K, &st);
+            }
+            if (pl && pl->g_sk > 0 && pl->grid > cus && pl->ipt > 64) {
+                delete pl;
+                continue;
+            }
+        }
+        // The FP32 one splits up to a tile and a half per CU, a third from 160 slabs a
+        // tile on (768x2304x768, 432 tiles, 34.4 us against 34.0 on the 128x128
+        // tile; 510x859x5621, 112 of 176 slabs, 56.0 against 53.3; 192x1728x7104,
+        // 81 of 222, 52.9 against 63.4).
+        if (pl && !named && base->dtype == DT_F32 && v == 1 && pl->g_sk > 0 && pl->occ > 0) {
+            const int64_t cus = pl->p / pl->occ;
+            if (2 * int64_t(pl->t) > 3 * cus || (pl->ipt >= 160 && 3 * int64_t(pl->t) > cus)) {
+                delete pl;
+                continue;
+            }
+        }
         if (!pl) {
             if (st == SKGEMM_ERR_HIP) {
                 for (skgemm_plan_s* c : cand) delete c;
@@ -731,7 +803,8 @@ static skgemm_status_t plan_variants(skgemm_plan_s* base, const skgemm_options_t
     for (skgemm_plan_s* c : cand) {
         if (!c) continue;
         double tc = 0.0;
-        const double t = plan_estimate(c, &tc);
+        double t = plan_estimate(c, &tc);
+        if (!named && is_quarter_variant(c->dtype, c->variant)) t /= kQuarterGain;
         if (!best || t < best_t || (t == best_t && tc < best_c)) {
             delete best;
             best = c;

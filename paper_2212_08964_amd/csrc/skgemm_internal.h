@@ -38,6 +38,8 @@ constexpr TileCfg kTileF64 = {64, 64, 16, 2};
 constexpr TileCfg kTileF64L = {128, 128, 16, 2};   // fp64, large-tile variant
 constexpr TileCfg kTile16R32 = {32, 32, 256, 4};  // bf16 and f16, streaming tile for M <= 32
 constexpr TileCfg kTile16R64 = {64, 32, 256, 3};  // bf16 and f16, streaming tile for M <= 64
+constexpr TileCfg kTile16Q = {64, 64, 64, 3};     // bf16 and f16, quarter-size tile
+constexpr TileCfg kTileF32S = {64, 64, 32, 2};    // fp32, quarter-size tile
 constexpr TileCfg kTile16D = {128, 128, 64, 3};   // bf16 and f16, small tile on three LDS stages
 
 // One problem of a grouped launch (device table entry, 128 bytes).  Shapes are
@@ -118,12 +120,15 @@ struct KArgs {
 // where the grid fits one workgroup per CU, never as a candidate of its own.
 // 9: the same with the convolution gather, substituted for variant 4.
 // 10 and 11: the streaming tiles of 32 and 64 rows (both operands K-contiguous).
-constexpr int kVariants = 12;
+// 12: the quarter-size 64x64 16-bit tile.
+constexpr int kVariants = 13;
 constexpr int kVariantDeep = 8;
 constexpr int kVariantDeepConv = 9;
+constexpr int kVariantQuarter = 12;
 constexpr int kVariantStream32 = 10;
 constexpr int kVariantStream64 = 11;
 constexpr bool is_stream_variant(int v) { return v == kVariantStream32 || v == kVariantStream64; }
+constexpr bool is_quarter_variant(int dt, int v) { return v == kVariantQuarter || (dt == DT_F32 && v == 1); }
 constexpr bool is_conv_variant(int v) { return v == 3 || v == 4 || v == 7 || v == 9; }
 
 // Copy `lines` lines of `cols` elements of eb bytes (line i at src + i * ld)

@@ -35,7 +35,9 @@
 //    lanes of a cycle on distinct banks (the other type's position would give
 //    two-way conflicts).
 //  * MN-contiguous operand: [k][512 bytes of rows]; chunk c of row k sits at
-//    position c ^ 4 (k mod 4) ^ 2 ((k / 8) mod 2) for 16-bit types (read with
+//    position c ^ 4 (k mod 4) ^ 2 ((k / 8) mod 2) for 16-bit types (128-byte
+//    rows, two to a cycle of the banks: c ^ 2 ((k / 2) mod 2) ^ 4 ((k / 8) mod 2);
+//    read with
 //    the LDS transpose read, four k of one column per lane; two groups of 16
 //    lanes eight k apart are served together) and c ^ 8 ((k / 4) mod 2) for
 //    FP32 (read with plain 4-byte reads).
@@ -110,6 +112,17 @@ template <> struct Cfg<DT_F16, 7> : Cfg<DT_F16, 6> { static constexpr bool CONV 
 template <> struct Cfg<DT_BF16, 7> : Cfg<DT_BF16, 6> { static constexpr bool CONV = true; };
 template <> struct Cfg<DT_F16, 9> : Cfg<DT_F16, 8> { static constexpr bool CONV = true; };
 template <> struct Cfg<DT_BF16, 9> : Cfg<DT_BF16, 8> { static constexpr bool CONV = true; };
+
+// Quarter-size tiles for problems with few 128x128 tiles: four 64x64 tiles in
+// the place of one 128x128 tile cut into four shares, so that the CUs are filled
+// without partial tiles (the hand-over of a 128x128 tile's shares, 3-4 us, is
+// as long as such a problem's whole MAC loop).  Bound by launch, first loads and
+// epilogue (about 6 us of BF16 1024^3's 8.9; before, 128x128 tiles in 4 shares,
+// 13.0; FP32 384x384x1024 13.0 against 19.5).  Wave tiles of 32x32 keep the LDS
+// reads within the MFMAs' time and 3 (FP32 4) workgroups on a CU.
+template <> struct Cfg<DT_F16, 12> { static constexpr int EB = 2, BM = kTile16Q.bm, BN = kTile16Q.bn, BK = kTile16Q.bk, WM = 2, WN = 2, NS = kTile16Q.ns, WPE = 3; };
+template <> struct Cfg<DT_BF16, 12> : Cfg<DT_F16, 12> {};
+template <> struct Cfg<DT_F32, 1> { static constexpr int EB = 4, BM = kTileF32S.bm, BN = kTileF32S.bn, BK = kTileF32S.bk, WM = 2, WN = 2, NS = kTileF32S.ns, WPE = 4; };
 
 // Streaming tiles for problems of at most 32 or 64 rows whose B is a
 // K-contiguous weight.  Such a product is bound by the bytes of B from HBM: a
@@ -221,6 +234,7 @@ __device__ __forceinline__ int swz(int row) {
     else if constexpr (KC && ROWB == 128) return (row & 7) ^ ((row >> 3) & 1);
     else if constexpr (KC) return (row >> 2) & 3;          // 64-byte rows: 4 chunks
     else if constexpr (EB == 4) return 8 * ((row >> 2) & 1);
+    else if constexpr (EB == 2 && ROWB == 128) return (2 * ((row >> 1) & 1)) ^ (4 * ((row >> 3) & 1));
     else if constexpr (EB == 2) return (4 * (row & 3)) ^ (2 * ((row >> 3) & 1));
     else return 4 * (row & 3);
 }
@@ -246,8 +260,8 @@ struct Slab {
     static constexpr int PER_WAVE = BLOCKS / NW;
     static_assert(!KC || BK * EB == 64 || BK * EB == 128 || ((BK * EB == 256 || BK * EB == 512) && EB == 2),
                   "K-contiguous slab rows must be 64 or 128 bytes (256 or 512 for 16-bit types)");
-    static_assert(KC || ROWB == 1024 || ROWB == 512 || ROWB == 256,
-                  "MN-contiguous slab rows must be 256, 512 or 1024 bytes");
+    static_assert(KC || ROWB == 1024 || ROWB == 512 || ROWB == 256 || (ROWB == 128 && EB == 2),
+                  "MN-contiguous slab rows must be 256, 512 or 1024 bytes (128 for 16-bit types)");
     static_assert(BLOCKS % NW == 0, "slab must split evenly over the waves");
 
     // Rows between a lane's consecutive chunks.  Where the swizzle repeats after
@@ -255,7 +269,7 @@ struct Slab {
     // per lane serves them all (a vector addition each, behind the MFMAs, for
     // registers the accumulators need); else every chunk has its own.
     static constexpr int ROWS_STEP = NW * 1024 / ROWB;
-    static constexpr bool UNIFORM = ROWS_STEP % 16 == 0 || (EB != 2 && !KC && ROWS_STEP % (EB == 4 ? 8 : 4) == 0);
+    static constexpr bool UNIFORM = EB <= 2 && ROWS_STEP % 16 == 0;
     uint32_t voff[UNIFORM ? 1 : PER_WAVE];     // byte offsets of the lane's chunks from the slab origin
     uint32_t vstep;              // UNIFORM: bytes between them
     const unsigned char* base;   // operand address of (outer o0, k of the first iteration)
