@@ -658,11 +658,13 @@ static skgemm_plan_s* build_variant(const skgemm_plan_s* base, int v, const skge
 // to 16384 columns and 1024 to 8192 k, odd sizes among them: 1.2-1.7x the best
 // of the other tiles up to one tile per CU, 0.98-1.27x above): always, but for
 // a short last wave of short tiles (13x10715x1152, 335 tiles of 5 slabs: 16.1
-// us against 12.8; 16x20000x333, 625 of 2: 20.3 against 10.2).  33 to 64 rows: where its tiles fit the CUs in one wave and
-// the rows of both operands start on 128-byte lines (1.0-1.32x); with more
-// tiles, or every run of a slab across a line more, its half of A a slab costs
-// more than the longer runs gain (64x11000x5000 40.7 us on the 64x256 tile, 50.2
-// here).
+// us against 12.8; 16x20000x333, 625 of 2: 20.3 against 10.2), and for short
+// tiles above one per CU whose last slab is mostly padding (k padded by a
+// twentieth: 24x17000x2176, 30.2 against 27.5; 1x8700x2176, 17.5 against 16.7).  33
+// to 64 rows: where its tiles fit the CUs in one wave and the rows of both
+// operands start on 128-byte lines (1.0-1.32x); with more tiles, or every run of
+// a slab across a line more, its half of A a slab costs more than the longer
+// runs gain (64x11000x5000 40.7 us on the 64x256 tile, 50.2 here).
 static int stream_variant(const skgemm_plan_s* base, const skgemm_options_t& o, const int64_t* M, const int64_t* N,
                           const int64_t* K) {
     if (base->G || base->conv || base->batch != 1 || !base->akc || !base->bkc || o.policy != SKGEMM_POLICY_AUTO ||
@@ -675,8 +677,10 @@ static int stream_variant(const skgemm_plan_s* base, const skgemm_options_t& o, 
     if (v < 0 || !kernel_exists(base->dtype, true, true, v)) return -1;
     int cus = o.num_cus, occ = 1;
     if (!cus && device_capacity(base->dtype, true, true, v, &cus, &occ) != SKGEMM_OK) return -1;
-    const int64_t t = cdiv(cols, kTile16R32.bn), rem = t % cus;
-    if (t > cus && (v == kVariantStream64 || (cdiv(K[0], kTile16R32.bk) < 8 && 5 * rem < 3 * cus && rem))) return -1;
+    const int64_t t = cdiv(cols, kTile16R32.bn), rem = t % cus, ipt = cdiv(K[0], kTile16R32.bk);
+    if (t > cus && (v == kVariantStream64 || (ipt < 8 && 5 * rem < 3 * cus && rem) ||
+                    (ipt < 12 && 20 * (ipt * kTile16R32.bk - K[0]) >= K[0])))
+        return -1;
     return v;
 }
 

@@ -114,3 +114,13 @@ def test_stream_rule():
         with pytest.raises(s.SkgemmError) as e:
             tile(16, 4096, 4096, lb=s.ROW_MAJOR, tile=t)
         assert e.value.status == s.ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("M,N,K,stream", [(24, 17000, 2176, False), (1, 8700, 2176, False), (24, 17000, 2048, True),
+                                          (1, 8192, 2176, True), (24, 17000, 4096, True), (1, 9663, 2900, True)])
+def test_stream_rule_padded_last_slab(M, N, K, stream):
+    """Above one tile per CU, short tiles whose last slab is mostly padding stay
+    on the other tiles."""
+    s = sk()
+    p = s.Plan(M, N, K, lb=s.COL_MAJOR, ta=s.BF16, num_cus=256, occupancy=2)
+    assert (p.info()["tile"][:3] in TILES) == stream
