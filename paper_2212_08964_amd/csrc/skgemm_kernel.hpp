@@ -276,6 +276,7 @@ struct Slab {
     int64_t bytes;               // operand bytes from base to its end
     int64_t step;                // bytes between consecutive k-iterations
     uint32_t ldb;                // leading dimension, bytes
+    int nth;                     // PRODUCT: number of the next slab
     uint64_t ahead;              // address of the next slab to prepare (they are prepared in order) ...
     int64_t left;                // ... and the operand's bytes from there on
 
@@ -295,6 +296,7 @@ struct Slab {
         ldb = uint32_t(ld * EB);
         ahead = reinterpret_cast<uint64_t>(base);
         left = bytes;
+        nth = 0;
 #pragma unroll
         for (int j = 0; j < (UNIFORM ? 1 : PER_WAVE); ++j) voff[j] = chunk_off(j, tid);
         vstep = uint32_t(ROWS_STEP) * ldb;
@@ -330,6 +332,15 @@ struct Slab {
                                                  nrec(it), kBufferFlags);
     }
 
+    // Descriptor of slab `it` from the product.  FP32 K-contiguous slabs, whose loop
+    // has scalar slots to spare, run faster on it (2000x3000x1500, B row-major, 186.5 us
+    // against 189.4 with additions; B column-major 186.7 against 190.8).
+    static constexpr bool PRODUCT = EB == 4 && KC;
+    __device__ __forceinline__ i32x4 nth_desc(int it) const {
+        const uint64_t addr = reinterpret_cast<uint64_t>(base + (int64_t)it * step);
+        return i32x4{uni(int(uint32_t(addr))), uni(int(uint32_t(addr >> 32) & 0xffffu)), uni(nrec(it)), kBufferFlags};
+    }
+
     // The next slab's descriptor as four scalar words (base, stride 0, records,
     // flags), kept up by additions: the products it * step cost more scalar
     // instructions a slab than everything else the loop does on the scalar side.
@@ -363,7 +374,7 @@ struct Slab {
     // wholly inside the inner edge (no per-chunk checks).
     template <bool EDGE>
     __device__ __forceinline__ void issue(int k0, int K, int o0, int dout, uint32_t lds, int tid) {
-        const i32x4 d = next_desc();
+        const i32x4 d = PRODUCT ? nth_desc(nth++) : next_desc();
         if constexpr (EDGE) tid = opaque(tid);
         const bool tail = EDGE && (KC ? (k0 + BK > K) : (o0 + R > dout));
         const int lim = KC ? (K - k0) : (dout - o0);
@@ -807,6 +818,41 @@ struct Gemm {
             // B[k l/16][col l%16] of the k4 step; each 32x32 block is four
             // 16x16 MFMA blocks.
             const int l16 = lane & 15, kq = lane >> 4;
+            // Both operands K-contiguous: the next step's fragments are read ahead of a
+            // step's MFMAs (256x512x4096 38.5 us against 40.5; with an MN-contiguous
+            // operand, whose reads are twice as many, 2-13 % slower, as for FP32).
+            if constexpr (AKC && BKC) {
+                double af[2][FM][2], bf[2][FN][2];
+                auto read = [&](int s) {
+                    const int k = 4 * s + kq;
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+                            af[s & 1][i][h] = lds_f64<AKC, SA::ROWB>(As, wm * WTM + i * 32 + h * 16 + l16, k);
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+                            bf[s & 1][j][h] = lds_f64<BKC, SB::ROWB>(Bs, wn * WTN + j * 32 + h * 16 + l16, k);
+                };
+                read(0);
+#pragma unroll
+                for (int s = 0; s < BK / 4; ++s) {
+                    if (s + 1 < BK / 4) read(s + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+#pragma unroll
+                        for (int j = 0; j < FN; ++j)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                acc.v[i][j][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                                    af[s & 1][i][q >> 1], bf[s & 1][j][q & 1], acc.v[i][j][q], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                return;
+            }
 #pragma unroll
             for (int s = 0; s < BK / 4; ++s) {
                 const int k = 4 * s + kq;
@@ -829,12 +875,12 @@ struct Gemm {
                                                                                  acc.v[i][j][q], 0, 0, 0);
             }
         } else {
-            // Lane group g handles k = 8c + 4g + u of step (c, u).
+            // Lane group g handles k = 8c + 4g + u of step (c, u).  The first MFMAs need
+            // A's first fragment and B's, so A's others are read last.
 #pragma unroll
             for (int c = 0; c < BK / 8; ++c) {
                 f32x4 af[FM], bf[FN];
-#pragma unroll
-                for (int i = 0; i < FM; ++i) {
+                auto read_a = [&](int i) {
                     const int row = wm * WTM + i * 32 + l32;
                     if constexpr (AKC) {
                         af[i] = __builtin_bit_cast(f32x4, lds_row_chunk<EB, SA::ROWB>(As, row, 2 * c + g));
@@ -843,7 +889,8 @@ struct Gemm {
                         for (int u = 0; u < 4; ++u)
                             af[i][u] = *reinterpret_cast<const float*>(As + mn_addr<4, SA::ROWB>(8 * c + 4 * g + u, row));
                     }
-                }
+                };
+                read_a(0);
 #pragma unroll
                 for (int j = 0; j < FN; ++j) {
                     const int col = wn * WTN + j * 32 + l32;
@@ -855,6 +902,10 @@ struct Gemm {
                             bf[j][u] = *reinterpret_cast<const float*>(Bs + mn_addr<4, SB::ROWB>(8 * c + 4 * g + u, col));
                     }
                 }
+                if constexpr (AKC && BKC) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 1; i < FM; ++i) read_a(i);
+                if constexpr (AKC && BKC) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
 #pragma unroll
