@@ -124,11 +124,12 @@ def test_quarter_rule():
         assert e.value.status == s.ERR_UNSUPPORTED
 
 
-@pytest.mark.parametrize("M,N,K,large", [(859, 4882, 5625, True), (1205, 5927, 5656, True), (859, 4882, 5632, True),
-                                         (1152, 5120, 7424, False), (512, 2000, 3001, False), (192, 1136, 5059, False)])
+@pytest.mark.parametrize("M,N,K,large", [(2556, 1675, 2416, True), (2556, 1675, 2432, False), (1297, 3957, 3360, True),
+                                         (512, 2000, 3001, False), (192, 1136, 5059, False)])
 def test_small_fp8_tile_rule(M, N, K, large):
-    """Automatic FP8 plans weigh the small tile's misaligned runs (K not a multiple
-    of 128); small products and others with whole lines stay on it."""
+    """Automatic FP8 plans weigh the small tile's misaligned runs where K is not a
+    multiple of 128; with whole lines, and for small products, it stays."""
     s = sk()
-    kw = dict(lb=s.COL_MAJOR, ta=s.F8E4M3, tc=s.BF16, num_cus=256)
-    assert (s.Plan(M, N, K, **kw, occupancy=2).info()["tile"][:3] == (256, 256, 128)) == large
+    kw = dict(lb=s.COL_MAJOR, ta=s.F8E4M3, tc=s.BF16, num_cus=256, occupancy=2)
+    assert (s.Plan(M, N, K, **kw).info()["tile"][:3] == (256, 256, 128)) == large
+    assert s.Plan(M, N, K, **kw, tile=(128, 128, 128)).info()["tile"][:3] == (128, 128, 128)
