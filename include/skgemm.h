@@ -88,8 +88,9 @@ typedef struct {
     int32_t force_g;              /* >0: Stream-K grid size instead of the model's choice */
     int32_t tile_m, tile_n, tile_k;   /* 0 = the planner picks among the dtype's
                                          compiled tiles by modelled time; else must
-                                         name one: FP32 128x128x32; FP16/BF16
-                                         256x256x64, 128x128x64, 64x256x64 (A
+                                         name one: FP32 128x128x32 or 64x64x32;
+                                         FP16/BF16 64x64x64, 32x32x256 and 64x32x256
+                                         (both operands K-contiguous), 256x256x64, 128x128x64, 64x256x64 (A
                                          K-contiguous; picked automatically only
                                          where every launched problem has at most
                                          64 rows) or 256x64x64 (B K-contiguous; at
