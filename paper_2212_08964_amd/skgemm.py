@@ -531,8 +531,8 @@ def matmul(A, B, out=None, *, out_dtype=None, alpha=1.0, beta=0.0, scale_a=None,
     fast = (out is None and trace is None and beta == 0.0
             and not (check or (check is None and _check_runs)))
     if fast:
-        key = (A.shape, A.stride(), B.shape, B.stride(), A.dtype, B.dtype, A.device, out_dtype, policy, force_g,
-               hybrid_min_waves, tuple(tile) if tile else None, fixup, spin_limit)
+        key = (A.shape, A.stride(), B.shape, B.stride(), A.dtype, B.dtype, A.device, B.device, out_dtype,
+               policy, force_g, hybrid_min_waves, tuple(tile) if tile else None, fixup, spin_limit)
         ent = _fast_cache.get(key)
         if ent is not None:
             return _fast_run(ent, A, B, alpha, scale_a, scale_b)

@@ -1,0 +1,101 @@
+"""What the tensor layer refuses, on a first call and on a repeated one.
+
+A repeated call goes past the layout inference and the plan lookup, so its key
+must hold everything the skipped checks look at.  The library and the tensors
+are stand-ins that record launches: nothing here needs a GPU, and a pointer that
+would have reached a kernel shows up as a launch."""
+import itertools
+import math
+import types
+
+import pytest
+import torch
+
+from paper_2212_08964_amd import skgemm
+
+GPU, OTHER, HOST = torch.device("cuda:0"), torch.device("cuda:1"), torch.device("cpu")
+
+
+class Tensor:
+    """Shape, strides, type, device and an address."""
+
+    addresses = itertools.count(1 << 20, 1 << 12)
+
+    def __init__(self, *shape, dtype=torch.bfloat16, device=GPU, stride=None, pinned=False):
+        self.shape, self.dtype, self.device, self._pinned = torch.Size(shape), dtype, torch.device(device), pinned
+        self._stride = stride or tuple(math.prod(shape[i + 1:]) for i in range(len(shape)))
+        self._ptr = next(self.addresses)
+
+    is_cuda = property(lambda self: self.device.type == "cuda")
+
+    def get_device(self):
+        return self.device.index if self.is_cuda else -1
+
+    def dim(self):
+        return len(self.shape)
+
+    def stride(self, i=None):
+        return self._stride if i is None else self._stride[i]
+
+    def numel(self):
+        return self.shape.numel()
+
+    def data_ptr(self):
+        return self._ptr if self.numel() else 0
+
+    def is_pinned(self):
+        return self._pinned
+
+
+@pytest.fixture
+def launches(monkeypatch):
+    """Empty caches, and a library whose launches are recorded."""
+    seen = []
+    handle = object()
+
+    class Plan:
+        def __init__(self):
+            self.handle = handle
+
+        def workspace_size(self):
+            return 0
+
+        def run(self, *args, stream=None):
+            seen.append(args)
+
+    def fast(h, *args):
+        assert h is handle
+        seen.append(args)
+        return skgemm.OK
+
+    monkeypatch.setattr(skgemm, "lib", lambda: types.SimpleNamespace(skgemm_run=fast))
+    monkeypatch.setattr(skgemm, "get_plan", lambda *a: Plan())
+    monkeypatch.setattr(skgemm, "_fast_cache", {})
+    monkeypatch.setattr(skgemm, "_raw_stream", lambda dev: 0)
+    monkeypatch.setattr(torch, "empty", lambda shape, dtype=None, device=None: Tensor(*shape, dtype=dtype, device=device))
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda dev=None: types.SimpleNamespace(cuda_stream=0))
+    return seen
+
+
+def scale(**k):
+    return Tensor(1, dtype=torch.float32, **k)
+
+
+@pytest.mark.parametrize("scaled", [False, True])
+@pytest.mark.parametrize("device", [HOST, OTHER])
+def test_matmul_second_operand_elsewhere(launches, scaled, device):
+    """B in host memory or on another GPU is refused, also where the same shapes,
+    strides and types have run before."""
+    kw = dict(scale_a=scale(), scale_b=scale()) if scaled else {}
+    A, B = Tensor(64, 128), Tensor(128, 32)
+    away = Tensor(128, 32, device=device)
+    with pytest.raises(ValueError, match="same GPU"):
+        skgemm.matmul(A, away, **kw)
+    skgemm.matmul(A, B, **kw)
+    skgemm.matmul(A, B, **kw)
+    assert len(launches) == 2
+    with pytest.raises(ValueError, match="same GPU"):
+        skgemm.matmul(A, away, **kw)
+    with pytest.raises(ValueError, match="same GPU"):
+        skgemm.matmul(Tensor(64, 128, device=device), B, **kw)
+    assert len(launches) == 2
