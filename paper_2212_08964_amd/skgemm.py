@@ -572,8 +572,7 @@ def matmul(A, B, out=None, *, out_dtype=None, alpha=1.0, beta=0.0, scale_a=None,
     ws = workspace(nws, A.device, stream) if nws else None
     args = (A.data_ptr() if A.numel() else None, la[1], B.data_ptr() if B.numel() else None, lb[1],
             out.data_ptr() if out.numel() else None, lc[1], alpha, beta,
-            scale_a.data_ptr() if scale_a is not None else None,
-            scale_b.data_ptr() if scale_b is not None else None,
+            _scale_ptr(scale_a, A.device), _scale_ptr(scale_b, A.device),
             ws.data_ptr() if ws is not None else None, nws)
     if trace is None:
         plan.run(*args, stream=stream)
@@ -615,6 +614,16 @@ def _ws_ptr(nws, dev, stream):
     return ws.data_ptr()
 
 
+def _scale_ptr(s, dev):
+    """Address of a scale: one FP32 value the kernel can read (None for none)."""
+    import torch
+    if s is None:
+        return None
+    if s.dtype is not torch.float32 or s.numel() < 1 or (s.device != dev and not s.is_pinned()):
+        raise ValueError("a scale must hold an FP32 value in the operands' GPU (or pinned) memory")
+    return s.data_ptr()
+
+
 def _fast_run(ent, A, B, alpha, scale_a, scale_b):
     """matmul for a signature seen before: no layout inference, no plan lookup."""
     import torch
@@ -622,8 +631,7 @@ def _fast_run(ent, A, B, alpha, scale_a, scale_b):
     out = torch.empty((M, N), dtype=odt, device=dev)
     stream = _raw_stream(dev)
     st = fn(handle, A.data_ptr(), lda, B.data_ptr(), ldb, out.data_ptr(), ldc, float(alpha), 0.0,
-            scale_a.data_ptr() if scale_a is not None else None, scale_b.data_ptr() if scale_b is not None else None,
-            _ws_ptr(nws, dev, stream), nws, stream)
+            _scale_ptr(scale_a, dev), _scale_ptr(scale_b, dev), _ws_ptr(nws, dev, stream), nws, stream)
     if st != OK:
         raise SkgemmError(st, "skgemm_run")
     return out

@@ -99,3 +99,23 @@ def test_matmul_second_operand_elsewhere(launches, scaled, device):
     with pytest.raises(ValueError, match="same GPU"):
         skgemm.matmul(Tensor(64, 128, device=device), B, **kw)
     assert len(launches) == 2
+
+
+@pytest.mark.parametrize("bad", [dict(dtype=torch.float64), dict(dtype=torch.bfloat16), dict(device=HOST), dict(device=OTHER),
+                                 dict(shape=(0,))])
+@pytest.mark.parametrize("which", ["scale_a", "scale_b"])
+def test_matmul_scales(launches, bad, which):
+    """A scale is read as one FP32 value through its address: another type,
+    memory the kernel cannot read and no value at all are refused; pinned host
+    memory and a value among others are not."""
+    A, B = Tensor(64, 128), Tensor(128, 32)
+    kw = {"dtype": torch.float32, **{k: v for k, v in bad.items() if k != "shape"}}
+    wrong = Tensor(*bad.get("shape", (1,)), **kw)
+    for n in (0, 1):            # before and after a call of the same signature
+        with pytest.raises(ValueError, match="scale"):
+            skgemm.matmul(A, B, **{which: wrong})
+        assert len(launches) == n
+        for good in (scale(), scale(device=HOST, pinned=True), Tensor(4, dtype=torch.float32), Tensor(dtype=torch.float32)):
+            skgemm.matmul(A, B, **{which: good})
+            assert launches.pop()[8 if which == "scale_a" else 9] == good.data_ptr()
+        launches[:] = [None]
