@@ -276,7 +276,6 @@ struct Slab {
     int64_t bytes;               // operand bytes from base to its end
     int64_t step;                // bytes between consecutive k-iterations
     uint32_t ldb;                // leading dimension, bytes
-    int nth;                     // PRODUCT: number of the next slab
     uint64_t ahead;              // address of the next slab to prepare (they are prepared in order) ...
     int64_t left;                // ... and the operand's bytes from there on
 
@@ -296,7 +295,6 @@ struct Slab {
         ldb = uint32_t(ld * EB);
         ahead = reinterpret_cast<uint64_t>(base);
         left = bytes;
-        nth = 0;
 #pragma unroll
         for (int j = 0; j < (UNIFORM ? 1 : PER_WAVE); ++j) voff[j] = chunk_off(j, tid);
         vstep = uint32_t(ROWS_STEP) * ldb;
@@ -332,17 +330,18 @@ struct Slab {
                                                  nrec(it), kBufferFlags);
     }
 
-    // Descriptor of slab `it` from the product.  FP32 K-contiguous slabs, whose loop
-    // has scalar slots to spare, run faster on it (2000x3000x1500, B row-major, 186.5 us
-    // against 189.4 with additions; B column-major 186.7 against 190.8).
-    static constexpr bool PRODUCT = EB == 4 && KC;
+    // Descriptor of slab `it` (counted from the first) from the product: FP32 and
+    // FP64, whose loops have scalar slots to spare but no scalar registers.  With
+    // the additions' state below, the kernel's arguments went to vector lanes and
+    // back, 0.3-0.5 us a launch (FP64 64x128x88 8.7 us against 9.4, 337x471x299 13.3
+    // against 13.8; FP32 128x640x2944 26.0 against 27.5).
     __device__ __forceinline__ i32x4 nth_desc(int it) const {
         const uint64_t addr = reinterpret_cast<uint64_t>(base + (int64_t)it * step);
         return i32x4{uni(int(uint32_t(addr))), uni(int(uint32_t(addr >> 32) & 0xffffu)), uni(nrec(it)), kBufferFlags};
     }
 
-    // The next slab's descriptor as four scalar words (base, stride 0, records,
-    // flags), kept up by additions: the products it * step cost more scalar
+    // 16-bit types and FP8: the next slab's descriptor as four scalar words (base,
+    // stride 0, records, flags), kept up by additions: the products it * step cost more scalar
     // instructions a slab than everything else the loop does on the scalar side.
     __device__ __forceinline__ i32x4 next_desc() {
         const uint32_t hi = uint32_t(uint64_t(left) >> 32);
@@ -369,13 +368,12 @@ struct Slab {
     // Descriptor of the next slab (its first k is k0).
     __device__ __forceinline__ i32x4 prepare(int, int) { return next_desc(); }
 
-    // Issue the direct-to-LDS loads of the next slab, whose first k is k0, into
-    // the stage at LDS address `lds`.  EDGE = false: the caller knows the slab is
+    // Issue the direct-to-LDS loads of the slab with descriptor d, whose first k is
+    // k0, into the stage at LDS address `lds`.  EDGE = false: the caller knows the slab is
     // wholly inside the inner edge (no per-chunk checks).
     template <bool EDGE>
-    __device__ __forceinline__ void issue(int k0, int K, int o0, int dout, uint32_t lds, int tid) {
-        const i32x4 d = PRODUCT ? nth_desc(nth++) : next_desc();
-        if constexpr (EDGE) tid = opaque(tid);
+    __device__ __forceinline__ void issue(const i32x4& d, int k0, int K, int o0, int dout, uint32_t lds, int tid) const {
+        if constexpr (EDGE && UNIFORM) tid = opaque(tid);
         const bool tail = EDGE && (KC ? (k0 + BK > K) : (o0 + R > dout));
         const int lim = KC ? (K - k0) : (dout - o0);
         lds += uint32_t(uni(tid >> 6)) * 1024;
@@ -404,7 +402,7 @@ struct Slab {
 #pragma unroll
         for (int j = 0; j < PER_WAVE; ++j) {
             const int kp = keep(j, tail, lim, tid);
-            const uint32_t at = chunk_off(j, tid);
+            const uint32_t at = UNIFORM ? chunk_off(j, tid) : voff[UNIFORM ? 0 : j];
             // a chunk that starts past the operand's end has landed as zeros
             if (kp > 0 && kp < VE && at < nr) {
                 unsigned char* dst = lds + (w + j * NW) * 1024 + lane * 16;
@@ -517,8 +515,7 @@ struct ConvSlab {
     __device__ __forceinline__ uint32_t off() const { return voff[J]; }
 
     template <bool EDGE>
-    __device__ __forceinline__ void issue(int k0, int, int, int, uint32_t lds, int tid) {
-        const i32x4 d = prepare(k0, tid);
+    __device__ __forceinline__ void issue(const i32x4& d, int, int, int, int, uint32_t lds, int tid) const {
         lds += uint32_t(uni(tid >> 6)) * 1024;
 #pragma unroll
         for (int j = 0; j < PER_WAVE; ++j) dma16(d, voff[j], lds + j * NW * 1024);
@@ -818,10 +815,11 @@ struct Gemm {
             // B[k l/16][col l%16] of the k4 step; each 32x32 block is four
             // 16x16 MFMA blocks.
             const int l16 = lane & 15, kq = lane >> 4;
-            // Both operands K-contiguous: the next step's fragments are read ahead of a
-            // step's MFMAs (256x512x4096 38.5 us against 40.5; with an MN-contiguous
-            // operand, whose reads are twice as many, 2-13 % slower, as for FP32).
-            if constexpr (AKC && BKC) {
+            // The 64x64 tile with both operands K-contiguous reads the next step's
+            // fragments ahead of a step's MFMAs (256x512x4096 38.5 us against 40.5; with
+            // an MN-contiguous operand, whose reads are twice as many, 2-13 % slower, as
+            // for FP32; the 128x128 tile 3 % slower: 1408x512x1152 46.7 against 45.3).
+            if constexpr (AKC && BKC && FM == 1) {
                 double af[2][FM][2], bf[2][FN][2];
                 auto read = [&](int s) {
                     const int k = 4 * s + kq;
@@ -966,11 +964,11 @@ struct Gemm {
         const int ahead = it + NS - 1;
         if (ahead < kend) {
             if (ahead < kedge) {
-                sa.template issue<false>(ahead * BK, a.K, m0, a.M, lds_addr(nxt), tid);
-                sb.template issue<false>(ahead * BK, a.K, n0, a.N, lds_addr(nxt) + SA::BYTES, tid);
+                sa.template issue<false>(sa.nth_desc(ahead - kbeg), ahead * BK, a.K, m0, a.M, lds_addr(nxt), tid);
+                sb.template issue<false>(sb.nth_desc(ahead - kbeg), ahead * BK, a.K, n0, a.N, lds_addr(nxt) + SA::BYTES, tid);
             } else {
-                sa.template issue<true>(ahead * BK, a.K, m0, a.M, lds_addr(nxt), tid);
-                sb.template issue<true>(ahead * BK, a.K, n0, a.N, lds_addr(nxt) + SA::BYTES, tid);
+                sa.template issue<true>(sa.nth_desc(ahead - kbeg), ahead * BK, a.K, m0, a.M, lds_addr(nxt), tid);
+                sb.template issue<true>(sb.nth_desc(ahead - kbeg), ahead * BK, a.K, n0, a.N, lds_addr(nxt) + SA::BYTES, tid);
             }
         }
         compute(cur, cur + SA::BYTES, acc, wm, wn, lane);
@@ -997,6 +995,13 @@ struct Gemm {
                 ...);
     }
 
+    // Descriptor of slab `it`, the n-th of the pipeline.
+    template <class S>
+    static __device__ __forceinline__ i32x4 desc(S& s, int n, int it, int tid) {
+        if constexpr (kSeam) return s.prepare(it * BK, tid);
+        else return s.nth_desc(n);
+    }
+
     // Slab kbeg + J into stage J, checked from kedge on.
     template <int J>
     static __device__ __forceinline__ void prologue_one(const Prob& a, SA& sa, SB& sb, int kbeg,
@@ -1005,11 +1010,11 @@ struct Gemm {
         const int it = kbeg + J;
         if (it >= kend) return;
         if (it < kedge) {
-            sa.template issue<false>(it * BK, a.K, m0, a.M, lds_addr(st.template at<J>()), tid);
-            sb.template issue<false>(it * BK, a.K, n0, a.N, lds_addr(st.template at<J>()) + SA::BYTES, tid);
+            sa.template issue<false>(desc(sa, J, it, tid), it * BK, a.K, m0, a.M, lds_addr(st.template at<J>()), tid);
+            sb.template issue<false>(desc(sb, J, it, tid), it * BK, a.K, n0, a.N, lds_addr(st.template at<J>()) + SA::BYTES, tid);
         } else {
-            sa.template issue<true>(it * BK, a.K, m0, a.M, lds_addr(st.template at<J>()), tid);
-            sb.template issue<true>(it * BK, a.K, n0, a.N, lds_addr(st.template at<J>()) + SA::BYTES, tid);
+            sa.template issue<true>(desc(sa, J, it, tid), it * BK, a.K, m0, a.M, lds_addr(st.template at<J>()), tid);
+            sb.template issue<true>(desc(sb, J, it, tid), it * BK, a.K, n0, a.N, lds_addr(st.template at<J>()) + SA::BYTES, tid);
         }
     }
 
@@ -1231,12 +1236,12 @@ struct Gemm {
     }
 
     static __device__ __forceinline__ void issue_a(const Prob& a, SA& sa, bool edge, int it, int m0, uint32_t lds, int tid) {
-        if (edge) sa.template issue<true>(it * BK, a.K, m0, a.M, lds, tid);
-        else sa.template issue<false>(it * BK, a.K, m0, a.M, lds, tid);
+        if (edge) sa.template issue<true>(sa.prepare(it * BK, tid), it * BK, a.K, m0, a.M, lds, tid);
+        else sa.template issue<false>(sa.prepare(it * BK, tid), it * BK, a.K, m0, a.M, lds, tid);
     }
     static __device__ __forceinline__ void issue_b(const Prob& a, SB& sb, bool edge, int it, int n0, uint32_t lds, int tid) {
-        if (edge) sb.template issue<true>(it * BK, a.K, n0, a.N, lds, tid);
-        else sb.template issue<false>(it * BK, a.K, n0, a.N, lds, tid);
+        if (edge) sb.template issue<true>(sb.prepare(it * BK, tid), it * BK, a.K, n0, a.N, lds, tid);
+        else sb.template issue<false>(sb.prepare(it * BK, tid), it * BK, a.K, n0, a.N, lds, tid);
     }
 
     // ---- streaming tiles (WK waves split the slab's k) and the 64-row and
