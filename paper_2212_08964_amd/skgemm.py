@@ -527,15 +527,15 @@ def matmul(A, B, out=None, *, out_dtype=None, alpha=1.0, beta=0.0, scale_a=None,
     ``check`` (default: set_error_checks) synchronises after the launch and
     raises SkgemmError(ERR_TIMEOUT), with the workspace cleared, if a fix-up
     wait expired."""
-    import torch
     fast = (out is None and trace is None and beta == 0.0
             and not (check or (check is None and _check_runs)))
     if fast:
-        key = (A.shape, A.stride(), B.shape, B.stride(), A.dtype, B.dtype, A.device, B.device, out_dtype,
+        key = (A.shape, A.stride(), B.shape, B.stride(), A.dtype, B.dtype, A.get_device(), B.get_device(), out_dtype,
                policy, force_g, hybrid_min_waves, tuple(tile) if tile else None, fixup, spin_limit)
         ent = _fast_cache.get(key)
         if ent is not None:
             return _fast_run(ent, A, B, alpha, scale_a, scale_b)
+    import torch
     dts = _torch_dtypes()
     if A.dim() != 2 or B.dim() != 2 or A.shape[1] != B.shape[0]:
         raise ValueError("matmul needs A (M x K) and B (K x N)")
@@ -586,22 +586,26 @@ def matmul(A, B, out=None, *, out_dtype=None, alpha=1.0, beta=0.0, scale_a=None,
     if fast and M * N * K > 0 and len(_fast_cache) < 4096:
         # everything this call derived from the tensors' shapes, strides and
         # types, for the next call with the same signature
-        _fast_cache[key] = (lib().skgemm_run, plan.handle, la[1], lb[1], lc[1], nws, M, N, out.dtype, A.device,
-                            plan)
+        _fast_cache[key] = (lib().skgemm_run, plan.handle, la[1], lb[1], lc[1], nws, torch.empty, (M, N), out.dtype,
+                            A.device, plan)
     return out
 
 
 _fast_cache = {}
 
 
+_stream_of = None
+
+
 def _raw_stream(device):
     """hipStream_t of the device's current stream (torch's raw accessor when it
     has one: it skips building a Stream object)."""
-    import torch
-    get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if get is not None:
-        return get(device.index)
-    return torch.cuda.current_stream(device).cuda_stream
+    global _stream_of
+    if _stream_of is None:
+        import torch
+        _stream_of = getattr(torch._C, "_cuda_getCurrentRawStream",
+                             lambda index: torch.cuda.current_stream(index).cuda_stream)
+    return _stream_of(device.index)
 
 
 def _ws_ptr(nws, dev, stream):
@@ -616,22 +620,23 @@ def _ws_ptr(nws, dev, stream):
 
 def _scale_ptr(s, dev):
     """Address of a scale: one FP32 value the kernel can read (None for none)."""
-    import torch
     if s is None:
         return None
-    if s.dtype is not torch.float32 or s.numel() < 1 or (s.device != dev and not s.is_pinned()):
+    ptr = s.data_ptr()          # 0: no element
+    if not ptr or _TORCH_DT.get(s.dtype) != F32 or (s.get_device() != dev.index and not s.is_pinned()):
         raise ValueError("a scale must hold an FP32 value in the operands' GPU (or pinned) memory")
-    return s.data_ptr()
+    return ptr
 
 
 def _fast_run(ent, A, B, alpha, scale_a, scale_b):
     """matmul for a signature seen before: no layout inference, no plan lookup."""
-    import torch
-    fn, handle, lda, ldb, ldc, nws, M, N, odt, dev, _plan = ent
-    out = torch.empty((M, N), dtype=odt, device=dev)
+    fn, handle, lda, ldb, ldc, nws, empty, shape, odt, dev, _plan = ent
+    sa = _scale_ptr(scale_a, dev) if scale_a is not None else None
+    sb = _scale_ptr(scale_b, dev) if scale_b is not None else None
+    out = empty(shape, dtype=odt, device=dev)
     stream = _raw_stream(dev)
-    st = fn(handle, A.data_ptr(), lda, B.data_ptr(), ldb, out.data_ptr(), ldc, float(alpha), 0.0,
-            _scale_ptr(scale_a, dev), _scale_ptr(scale_b, dev), _ws_ptr(nws, dev, stream), nws, stream)
+    st = fn(handle, A.data_ptr(), lda, B.data_ptr(), ldb, out.data_ptr(), ldc, float(alpha), 0.0, sa, sb,
+            _ws_ptr(nws, dev, stream) if nws else None, nws, stream)
     if st != OK:
         raise SkgemmError(st, "skgemm_run")
     return out
