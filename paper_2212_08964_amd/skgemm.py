@@ -11,6 +11,7 @@ execution path.
 from __future__ import annotations
 
 import ctypes
+import itertools
 import os
 import struct
 import threading
@@ -695,8 +696,9 @@ def grouped_matmul(As, Bs, Cs=None, *, out_dtype=None, alpha=1.0, beta=0.0, poli
     fast = (Cs is None and table is None and trace is None and beta == 0.0 and dev.type == "cuda"
             and not (check or (check is None and _check_runs)) and not torch.cuda.is_current_stream_capturing())
     if fast:
-        fkey = (tuple([(t.shape, t.stride()) for t in As]), tuple([(t.shape, t.stride()) for t in Bs]), As[0].dtype,
-                dev, out_dtype, policy, force_g, hybrid_min_waves, tuple(tile) if tile else None, spin_limit)
+        fkey = (tuple([(t.shape, t.stride(), t.dtype, t.get_device()) for t in As]),
+                tuple([(t.shape, t.stride(), t.dtype, t.get_device()) for t in Bs]),
+                out_dtype, policy, force_g, hybrid_min_waves, tuple(tile) if tile else None, spin_limit)
         ent = _gfast_cache.get(fkey)
         if ent is not None and torch.cuda.current_device() == dev.index:
             return _grouped_fast_run(ent, As, Bs, alpha)
@@ -706,6 +708,10 @@ def grouped_matmul(As, Bs, Cs=None, *, out_dtype=None, alpha=1.0, beta=0.0, poli
         if beta != 0.0:
             raise ValueError("beta != 0 needs Cs")
         Cs = [torch.empty((A.shape[0], B.shape[1]), dtype=out_dtype, device=dev) for A, B in zip(As, Bs)]
+    # (an operand without elements is never read)
+    if any(t.numel() and (t.dtype != As[0].dtype or t.device != dev) for t in itertools.chain(As, Bs)) or \
+            any(C.numel() and (C.dtype != Cs[0].dtype or C.device != dev) for C in Cs):
+        raise ValueError("all operands (and all results) of a group must have one dtype and live on one GPU")
     pa, pb, pc = _pick(As, ROW_MAJOR), _pick(Bs, COL_MAJOR), _pick(Cs, ROW_MAJOR)
     if pa is None or pb is None or pc is None:
         raise ValueError("all A (B, C) of a group must share one layout")

@@ -73,8 +73,49 @@ def launches(monkeypatch):
     monkeypatch.setattr(skgemm, "_fast_cache", {})
     monkeypatch.setattr(skgemm, "_raw_stream", lambda dev: 0)
     monkeypatch.setattr(torch, "empty", lambda shape, dtype=None, device=None: Tensor(*shape, dtype=dtype, device=device))
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda dev=None: types.SimpleNamespace(cuda_stream=0))
     return seen
+
+
+@pytest.fixture
+def grouped(launches, monkeypatch):
+    """The same for grouped launches; a record is the list of GroupArgs fields of every problem."""
+
+    class Plan:
+        handle = object()
+
+        def __init__(self, Ms, *a, **k):
+            self.n = len(Ms)
+
+        def workspace_size(self):
+            return 0
+
+        def table(self, args):
+            launches.append([list(a) for a in args])
+            return bytes(128 * self.n)
+
+        def grouped_run(self, *a):
+            pass
+
+    def table(handle, args, host, nbytes):
+        n = nbytes // 128
+        launches.append([[a.A, a.lda, a.B, a.ldb, a.C, a.ldc, a.alpha, a.beta] for a in args[:n]])
+        return skgemm.OK
+
+    def empty(shape, dtype=None, device=None, pin_memory=False):
+        return Tensor(*((shape,) if isinstance(shape, int) else shape), dtype=dtype, device=device or HOST)
+
+    monkeypatch.setattr(skgemm, "lib", lambda: types.SimpleNamespace(skgemm_grouped_table=table))
+    monkeypatch.setattr(skgemm, "GroupedPlan", Plan)
+    monkeypatch.setattr(skgemm, "_gplan_cache", {})
+    monkeypatch.setattr(skgemm, "_gfast_cache", {})
+    monkeypatch.setattr(torch, "empty", empty)
+    monkeypatch.setattr(Tensor, "copy_", lambda self, src, non_blocking=False: self, raising=False)
+    monkeypatch.setattr(torch, "frombuffer",
+                        lambda b, dtype: types.SimpleNamespace(to=lambda dev: Tensor(len(b), dtype=dtype, device=dev)))
+    return launches
 
 
 def scale(**k):
@@ -119,3 +160,28 @@ def test_matmul_scales(launches, bad, which):
             skgemm.matmul(A, B, **{which: good})
             assert launches.pop()[8 if which == "scale_a" else 9] == good.data_ptr()
         launches[:] = [None]
+
+
+def group(**odd):
+    """Two problems; `odd` replaces the second A's or B's properties: (name, {...})."""
+    As, Bs = [Tensor(8, 64), Tensor(24, 64)], [Tensor(64, 32), Tensor(64, 32)]
+    for name, k in odd.items():
+        {"A": As, "B": Bs}[name][1] = Tensor(*{"A": (24, 64), "B": (64, 32)}[name], **k)
+    return As, Bs
+
+
+@pytest.mark.parametrize("which", ["A", "B"])
+@pytest.mark.parametrize("odd", [dict(dtype=torch.float16), dict(dtype=torch.float32), dict(device=HOST), dict(device=OTHER)])
+def test_grouped_mixed_operands(grouped, which, odd):
+    """Every operand of a group has one type and one GPU: another is refused on
+    the first call and after a call of the same shapes and strides."""
+    for n in (0, 2):
+        with pytest.raises(ValueError, match="one dtype"):
+            skgemm.grouped_matmul(*group(**{which: odd}))
+        assert len(grouped) == n
+        if n == 0:
+            skgemm.grouped_matmul(*group())
+            skgemm.grouped_matmul(*group())
+    As, Bs = group()
+    with pytest.raises(ValueError, match="one dtype"):
+        skgemm.grouped_matmul(As, Bs, [Tensor(8, 32), Tensor(24, 32, dtype=torch.float32)])
