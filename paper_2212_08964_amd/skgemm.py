@@ -662,7 +662,7 @@ def _grouped_fast_run(ent, As, Bs, alpha):
     import torch
     plan, ldas, ldbs, ldcs, shapes, odt, dev, nbytes, nws, packer = ent
     Cs = [torch.empty(s, dtype=odt, device=dev) for s in shapes]
-    flat, al = [], float(alpha)
+    flat, al = [], ctypes.c_float(float(alpha)).value     # (infinite beyond FP32's range, where pack raises)
     for A, B, C, la, lb, lc in zip(As, Bs, Cs, ldas, ldbs, ldcs):
         flat += (A.data_ptr(), B.data_ptr(), C.data_ptr(), la, lb, lc, al, 0.0)
     # the caching host allocator reuses the block once the copy has finished

@@ -4,6 +4,7 @@ A repeated call goes past the layout inference and the plan lookup, so its key
 must hold everything the skipped checks look at.  The library and the tensors
 are stand-ins that record launches: nothing here needs a GPU, and a pointer that
 would have reached a kernel shows up as a launch."""
+import ctypes
 import itertools
 import math
 import types
@@ -185,3 +186,16 @@ def test_grouped_mixed_operands(grouped, which, odd):
     As, Bs = group()
     with pytest.raises(ValueError, match="one dtype"):
         skgemm.grouped_matmul(As, Bs, [Tensor(8, 32), Tensor(24, 32, dtype=torch.float32)])
+
+
+@pytest.mark.parametrize("alpha", [1.0, 0.1, -2.5, 1e39, -1e300, float("inf"), float("nan"), True, 3])
+def test_grouped_alpha(grouped, alpha):
+    """A repeated call hands on the alpha that the first one does: the FP32 value
+    of the argument, infinite beyond FP32's range."""
+    want = ctypes.c_float(float(alpha)).value
+    for _ in range(3):
+        skgemm.grouped_matmul(*group(), alpha=alpha)
+    assert len(grouped) == 3
+    for problem in itertools.chain(*grouped):
+        got = ctypes.c_float(problem[6]).value
+        assert got == want or (got != got and want != want)
