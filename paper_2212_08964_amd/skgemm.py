@@ -914,7 +914,16 @@ def conv2d(x, w, out=None, *, padding=(0, 0), stride=(1, 1), dilation=(1, 1), ou
     return out
 
 
-_qws = {}
+_qws_bytes = None
+
+
+def _quantize_ws_bytes():
+    global _qws_bytes
+    if _qws_bytes is None:
+        n = ctypes.c_size_t()
+        _check(lib().skgemm_quantize_workspace_size(ctypes.byref(n)), "skgemm_quantize_workspace_size")
+        _qws_bytes = n.value
+    return _qws_bytes
 
 
 def quantize_e4m3(X, layout="row", out=None, scale=None):
@@ -925,8 +934,8 @@ def quantize_e4m3(X, layout="row", out=None, scale=None):
     N x M row-major buffer), scale a 1-element FP32 device tensor."""
     import torch
     dts = _torch_dtypes()
-    if X.dim() != 2 or X.dtype not in (torch.float32, torch.bfloat16, torch.float16):
-        raise ValueError("quantize_e4m3 needs a 2-D FP32, BF16 or FP16 tensor")
+    if X.dim() != 2 or X.dtype not in (torch.float32, torch.bfloat16, torch.float16) or not X.is_cuda:
+        raise ValueError("quantize_e4m3 needs a 2-D FP32, BF16 or FP16 tensor on a GPU")
     rows, cols = X.shape
     lx = _layout(X)
     if lx is None:
@@ -942,14 +951,10 @@ def quantize_e4m3(X, layout="row", out=None, scale=None):
         raise ValueError("out needs one contiguous dimension")
     if scale is None:
         scale = torch.empty(1, dtype=torch.float32, device=X.device)
-    key = X.device.index
-    ws = _qws.get(key)
-    if ws is None:
-        n = ctypes.c_size_t()
-        _check(lib().skgemm_quantize_workspace_size(ctypes.byref(n)), "skgemm_quantize_workspace_size")
-        ws = torch.empty(n.value // 4, dtype=torch.float32, device=X.device)
-        _qws[key] = ws
-    stream = torch.cuda.current_stream(X.device).cuda_stream
+    # the maxima's buffer is this call's own: the allocator knows its stream, or the
+    # capture it belongs to, and no other call's kernels write between this one's
+    ws = torch.empty(_quantize_ws_bytes() // 4, dtype=torch.float32, device=X.device)
+    stream = _raw_stream(X.device)
     _check(lib().skgemm_quantize_e4m3(X.data_ptr() if X.numel() else None, dts[X.dtype], rows, cols, lx[0], lx[1],
                                       out.data_ptr() if out.numel() else None, lq[0], lq[1], scale.data_ptr(),
                                       ws.data_ptr(), ws.numel() * 4, stream), "skgemm_quantize_e4m3")

@@ -199,3 +199,58 @@ def test_grouped_alpha(grouped, alpha):
     for problem in itertools.chain(*grouped):
         got = ctypes.c_float(problem[6]).value
         assert got == want or (got != got and want != want)
+
+
+def test_quantizer_workspace_per_stream(launches, monkeypatch):
+    """The maxima of two quantising calls that may run at once (on two streams, or
+    queued by two threads) never share a buffer."""
+    seen = []
+
+    def quantize(x, dt, rows, cols, lx, ldx, q, lq, ldq, scale, ws, nbytes, stream):
+        seen.append((stream, ws, nbytes))
+        return skgemm.OK
+
+    def size(ref):
+        ref._obj.value = 4096
+        return skgemm.OK
+
+    stream = [0]
+    live = []
+
+    def empty(*shape, dtype=None, device=None):
+        live.append(Tensor(*(shape[0] if isinstance(shape[0], tuple) else shape), dtype=dtype, device=device))
+        return live[-1]
+
+    monkeypatch.setattr(skgemm, "lib", lambda: types.SimpleNamespace(skgemm_quantize_e4m3=quantize,
+                                                                    skgemm_quantize_workspace_size=size))
+    monkeypatch.setattr(skgemm, "_raw_stream", lambda dev: stream[0])
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda dev=None: types.SimpleNamespace(cuda_stream=stream[0]))
+    monkeypatch.setattr(torch, "empty", empty)
+    for stream[0] in (0, 7, 9, 7, 7):
+        skgemm.quantize_e4m3(Tensor(16, 32))
+    assert [s for s, _, _ in seen] == [0, 7, 9, 7, 7]
+    assert len({ws for _, ws, _ in seen}) == len(seen) and all(n == 4096 for _, _, n in seen)
+
+
+@pytest.mark.gpu
+def test_quantizer_two_streams():
+    """Two streams quantise matrices of very different magnitude without a
+    synchronisation between them: every scale and code is its own matrix's."""
+    dev = torch.device("cuda:0")
+    xs = [torch.randn(3000, 1700, device=dev) * f for f in (1.0, 1e4)]
+    refs = []
+    for x in xs:
+        s = (x.abs().max() / 448.0).cpu()
+        refs.append((torch.clamp(x.cpu() / s, -448.0, 448.0).to(torch.float8_e4m3fn).view(torch.uint8), s))
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    got = [[], []]
+    for _ in range(30):
+        for i, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                got[i].append(skgemm.quantize_e4m3(xs[i]))
+    torch.cuda.synchronize()
+    for i, (q0, s0) in enumerate(refs):
+        for q, s in got[i]:
+            assert torch.equal(s.cpu(), s0.reshape(1))
+            assert torch.equal(q.cpu().view(torch.uint8), q0)
