@@ -542,7 +542,7 @@ def matmul(A, B, out=None, *, out_dtype=None, alpha=1.0, beta=0.0, scale_a=None,
         raise ValueError("matmul needs A (M x K) and B (K x N)")
     if A.dtype != B.dtype or A.dtype not in dts:
         raise ValueError(f"unsupported input dtypes {A.dtype}, {B.dtype}")
-    if not A.is_cuda or A.device != B.device:
+    if not A.is_cuda or A.device != B.device or (out is not None and out.device != A.device):
         raise ValueError("operands must live on the same GPU")
     M, K = A.shape
     N = B.shape[1]
@@ -797,6 +797,8 @@ def batched_matmul(A, B, out=None, *, out_dtype=None, alpha=1.0, beta=0.0, polic
         raise ValueError("batched_matmul needs A (batch x M x K) and B (batch x K x N)")
     if A.dtype != B.dtype or A.dtype not in dts:
         raise ValueError(f"unsupported input dtypes {A.dtype}, {B.dtype}")
+    if not A.is_cuda or A.device != B.device or (out is not None and out.device != A.device):
+        raise ValueError("operands must live on the same GPU")
     batch, M, K = A.shape
     N = B.shape[2]
     la = _layout3(A, ROW_MAJOR)
@@ -873,6 +875,8 @@ def conv2d(x, w, out=None, *, padding=(0, 0), stride=(1, 1), dilation=(1, 1), ou
         raise ValueError("conv2d needs x (N, H, W, C) and w (K, R, S, C)")
     if x.dtype != w.dtype or x.dtype not in (torch.bfloat16, torch.float16):
         raise ValueError(f"unsupported input dtypes {x.dtype}, {w.dtype}")
+    if not x.is_cuda or x.device != w.device or (out is not None and out.device != x.device):
+        raise ValueError("operands must live on the same GPU")
     if not x.is_contiguous() or not w.is_contiguous():
         raise ValueError("conv2d needs contiguous channels-last x and w")
     pad, std, dil = tuple(padding), tuple(stride), tuple(dilation)

@@ -140,6 +140,8 @@ def test_matmul_second_operand_elsewhere(launches, scaled, device):
         skgemm.matmul(A, away, **kw)
     with pytest.raises(ValueError, match="same GPU"):
         skgemm.matmul(Tensor(64, 128, device=device), B, **kw)
+    with pytest.raises(ValueError, match="same GPU"):
+        skgemm.matmul(A, B, Tensor(64, 32, device=device), **kw)
     assert len(launches) == 2
 
 
@@ -254,3 +256,39 @@ def test_quantizer_two_streams():
         for q, s in got[i]:
             assert torch.equal(s.cpu(), s0.reshape(1))
             assert torch.equal(q.cpu().view(torch.uint8), q0)
+
+
+@pytest.mark.parametrize("device", [HOST, OTHER])
+@pytest.mark.parametrize("kind", ["batched", "conv"])
+def test_batched_and_conv_operand_elsewhere(launches, monkeypatch, kind, device):
+    """The second operand, and the result where one is given, are on the first's GPU."""
+
+    class Plan:
+        def __init__(self, *a, **k):
+            pass
+
+        def workspace_size(self):
+            return 0
+
+        def batched_run(self, *a, **k):
+            launches.append(a)
+
+        conv_run = batched_run
+
+    for name in ("BatchedPlan", "ConvPlan"):
+        monkeypatch.setattr(skgemm, name, Plan)
+    for name in ("_bplan_cache", "_bfast_cache", "_cplan_cache", "_cfast_cache"):
+        monkeypatch.setattr(skgemm, name, {})
+    monkeypatch.setattr(skgemm, "_layout3", lambda t, prefer: (skgemm.ROW_MAJOR, t.shape[2], t.stride(0)))
+    monkeypatch.setattr(Tensor, "is_contiguous", lambda self: True, raising=False)
+    shapes = {"batched": ((2, 8, 64), (2, 64, 16), (2, 8, 16)), "conv": ((2, 4, 4, 64), (8, 1, 1, 64), (2, 4, 4, 8))}[kind]
+    call = {"batched": skgemm.batched_matmul, "conv": skgemm.conv2d}[kind]
+    a, b = (Tensor(*s) for s in shapes[:2])
+    for n in (0, 1):
+        with pytest.raises(ValueError, match="same GPU"):
+            call(a, Tensor(*shapes[1], device=device))
+        with pytest.raises(ValueError, match="same GPU"):
+            call(a, b, Tensor(*shapes[2], device=device))
+        assert len(launches) == n
+        if n == 0:
+            call(a, b)
