@@ -1039,7 +1039,7 @@ struct Gemm {
     // are spread one by one between the MFMAs: issued in one burst ahead of
     // them, the memory pipeline's queue kept the waves from their MFMAs.
     static constexpr int FA = kHalf ? WTM / 16 : FM, FB = kHalf ? WTN / 16 : FN;
-    static constexpr bool kStream = kHalf && (WK > 1 || V == 5 || V == 6 || V == 7);
+    static constexpr bool kStream = kHalf && WK > 1;
     // Slot in which the last A fragment of the second step is read ahead, into
     // a spare register set, so that the seam does not wait for it (the FP8
     // 256x256 tile has no registers to spare).
@@ -1244,12 +1244,13 @@ struct Gemm {
         else sb.template issue<false>(sb.prepare(it * BK, tid), it * BK, a.K, n0, a.N, lds, tid);
     }
 
-    // ---- streaming tiles (WK waves split the slab's k) and the 64-row and
-    // 64-column ones
+    // ---- streaming tiles: WK waves split the slab's k
     //
     // Bound by the bytes in flight from HBM, not by the matrix cores: a slab is
     // waited for, and the stage consumed before it refilled at once, so NS - 1
-    // slabs are in flight while one is consumed.
+    // slabs are in flight while one is consumed.  (The 64-row and 64-column tiles,
+    // on two stages, run slab_loop: 29x1409x2183 on this loop 16.4 us, 15.1 there;
+    // 32x1016x272 10.9 and 10.0.)
     static __device__ __forceinline__ void stream_loop(const Prob& a, SA& sa, SB& sb, int kbeg, int kend, int kedge,
                                                        int m0, int n0, const Stages& st, Acc& acc, int tid) {
         constexpr int STEPS = BK / 32 / WK;    // k32 steps of a wave in a slab
