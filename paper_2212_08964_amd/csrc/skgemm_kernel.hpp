@@ -725,6 +725,82 @@ struct Gemm {
     struct Acc16 { f32x4 v[FM][FN][4]; };
     struct Acc64 { f64x4 v[FM][FN][4]; };
     using Acc = typename Pick<DT == DT_F64, Acc64, typename Pick<kHalf, Acc16, Acc32>::type>::type;
+    static __device__ __forceinline__ void zero(Acc& acc) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                if constexpr (DT == DT_F64) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc.v[i][j][q] = f64x4{0, 0, 0, 0};
+                } else if constexpr (kHalf) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc.v[i][j][q] = f32x4{0, 0, 0, 0};
+                } else {
+                    acc.v[i][j] = f32x16{0};
+                }
+            }
+    }
+    static __device__ __forceinline__ void add(Acc& sum, const Acc& acc) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                if constexpr (DT == DT_F64 || kHalf) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) sum.v[i][j][q] += acc.v[i][j][q];
+                } else {
+                    sum.v[i][j] += acc.v[i][j];
+                }
+            }
+    }
+
+    // The quarter-size and streaming tiles cut a tile's k into fewer shares than
+    // the larger tiles they stand in for, or not at all, and the rounding errors of
+    // a chain of FP32 additions grow with its length.  So these tiles sum in blocks of
+    // slabs: the MFMAs' accumulators are added to a running total and start again.
+    // With n MFMAs a block of N in the chain the errors' variance goes with
+    // n + N / n, least at n = sqrt(N), where no cut into shares is more exact.
+    // Relative error against 64 bits, 128x128 tile's shares / one chain / blocks:
+    // 640x1280x1827 BF16 with an FP32 result 1.1e-7 / 2.5e-7 / 1.0e-7, FP32
+    // 384x384x1024 1.9e-7 / 2.3e-7 / 1.2e-7.  The FP32 tile's launches take 2-6 %
+    // longer for it (504x376x136 9.0 us against 8.5), the others' do not.
+    static constexpr bool kBlocks32 = DT == DT_F32 && V == 1;
+    static constexpr bool kBlocks16 = kHalf && (V == kVariantQuarter || WK > 1);
+    // FP32: a block is a slab, 16 MFMAs.  The slabs take turns between two sets of
+    // accumulators, so that one is added up behind the other's MFMAs.
+    struct Turns {
+        Acc sum, odd;
+    };
+    // 16-bit types: two MFMAs a slab, blocks of sqrt(slabs / 2) slabs.  A 16-bit
+    // result's own rounding hides the sum's, so only FP32 results ask for them.
+    struct Blocks {
+        Acc sum;
+        int block, left;           // slabs in a block, and until the next one
+
+        __device__ __forceinline__ void start(int slabs, bool on) {
+            zero(sum);
+            block = on ? max(1, uni(int(__builtin_sqrtf(0.5f * float(slabs)) + 0.5f))) : slabs + 1;
+            left = block;
+        }
+        __device__ __forceinline__ void slab(Acc& acc) {
+            if (--left) return;
+            add(sum, acc);
+            zero(acc);
+            left = block;
+        }
+        __device__ __forceinline__ void finish(Acc& acc) {
+            add(sum, acc);
+            acc = sum;
+        }
+    };
+    struct NoSums {
+        __device__ __forceinline__ void start(int, bool) {}
+        __device__ __forceinline__ void slab(Acc&) {}
+        __device__ __forceinline__ void finish(Acc&) {}
+    };
+    using Sums = typename Pick<kBlocks32, Turns, typename Pick<kBlocks16, Blocks, NoSums>::type>::type;
+
     // 16-byte chunks of one block's accumulators per lane (partial tiles are
     // stored and read in this fragment order)
     static constexpr int CPB = DT == DT_F64 ? 8 : 4;
@@ -957,9 +1033,11 @@ struct Gemm {
     // Slabs of iterations from kedge on are loaded with per-chunk checks
     // against the operands' inner edges (and fixed up once they have landed);
     // the others lie wholly inside them.
+    template <int U>
     static __device__ __forceinline__ bool step(const Prob& a, SA& sa, SB& sb, int it, int kbeg,
                                                 int kend, int kedge, int m0, int n0, unsigned char* cur,
-                                                unsigned char* nxt, unsigned char* fix, Acc& acc, int tid) {
+                                                unsigned char* nxt, unsigned char* fix, Acc& acc, Sums& sums,
+                                                int tid) {
         const int lane = tid & 63, w = tid >> 6, wm = w / WN, wn = w % WN;
         const int ahead = it + NS - 1;
         if (ahead < kend) {
@@ -971,7 +1049,14 @@ struct Gemm {
                 sb.template issue<true>(sb.nth_desc(ahead - kbeg), ahead * BK, a.K, n0, a.N, lds_addr(nxt) + SA::BYTES, tid);
             }
         }
-        compute(cur, cur + SA::BYTES, acc, wm, wn, lane);
+        if constexpr (kBlocks32) {
+            Acc &mine = U ? sums.odd : acc, &last = U ? acc : sums.odd;
+            zero(mine);
+            compute(cur, cur + SA::BYTES, mine, wm, wn, lane);
+            add(sums.sum, last);
+        } else {
+            compute(cur, cur + SA::BYTES, acc, wm, wn, lane);
+        }
         const bool more = it + 1 < kend;
         if (more) {
             wait_slab(min(NS - 2, kend - 2 - it));
@@ -989,9 +1074,9 @@ struct Gemm {
     template <int... U>
     static __device__ __forceinline__ bool steps(const Prob& a, SA& sa, SB& sb, int kk, int kbeg,
                                                  int kend, int kedge, int m0, int n0, const Stages& st, Acc& acc,
-                                                 int tid, std::integer_sequence<int, U...>) {
-        return (step(a, sa, sb, kk + U, kbeg, kend, kedge, m0, n0, st.template at<U>(),
-                     st.template at<(U + NS - 1) % NS>(), st.template at<(U + 1) % NS>(), acc, tid) &&
+                                                 Sums& sums, int tid, std::integer_sequence<int, U...>) {
+        return (step<U>(a, sa, sb, kk + U, kbeg, kend, kedge, m0, n0, st.template at<U>(),
+                        st.template at<(U + NS - 1) % NS>(), st.template at<(U + 1) % NS>(), acc, sums, tid) &&
                 ...);
     }
 
@@ -1155,7 +1240,7 @@ struct Gemm {
     // are picked by offset: one copy of each body and one way through it keep the
     // accumulators in place.
     static __device__ __forceinline__ void slab_loop(const Prob& a, SA& sa, SB& sb, int kbeg, int kend, int kedge,
-                                                     int m0, int n0, const Stages& st, Acc& acc, int tid) {
+                                                     int m0, int n0, const Stages& st, Acc& acc, Sums& sums, int tid) {
         static_assert(BK * EB == 128 && FA >= 2 && FB >= 2 && WK == 1, "two steps a slab");
         using Slots = std::make_integer_sequence<int, FA>;
         const int lane = tid & 63, w = uni(tid >> 6), wm = (tid >> 6) / WN, wn = (tid >> 6) % WN;
@@ -1174,6 +1259,7 @@ struct Gemm {
         const int plain = min(kend, kedge);
         for (; it + NS < plain; ++it) {
             half_slab<0, false>(f, lds + cur, lds + cur + SA::BYTES, acc, rf, sa, sb, wm, wn, lane, Slots{});
+            sums.slab(acc);
             const int nxt = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
             // A wave that has its next slab and is at its MFMAs goes ahead of one that
             // waits (without it, workgroups sharing a CU drifted apart: the slowest
@@ -1189,6 +1275,7 @@ struct Gemm {
         __builtin_amdgcn_s_setprio(0);
         for (; it < kend; ++it) {
             half_slab<0, false>(f, lds + cur, lds + cur + SA::BYTES, acc, rf, sa, sb, wm, wn, lane, Slots{});
+            sums.slab(acc);
             const int nxt = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
             pin(acc);
             wait_slab(min(NS - 2, kend - 2 - it));
@@ -1202,6 +1289,7 @@ struct Gemm {
             half_slab<1, false>(f, lds + nxt, lds + nxt + SA::BYTES, acc, rf, sa, sb, wm, wn, lane, Slots{});
             cur = nxt;
         }
+        sums.finish(acc);
         // Every wave has read the last slab before the last barrier.
     }
 
@@ -1252,7 +1340,7 @@ struct Gemm {
     // on two stages, run slab_loop: 29x1409x2183 on this loop 16.4 us, 15.1 there;
     // 32x1016x272 10.9 and 10.0.)
     static __device__ __forceinline__ void stream_loop(const Prob& a, SA& sa, SB& sb, int kbeg, int kend, int kedge,
-                                                       int m0, int n0, const Stages& st, Acc& acc, int tid) {
+                                                       int m0, int n0, const Stages& st, Acc& acc, Sums& sums, int tid) {
         constexpr int STEPS = BK / 32 / WK;    // k32 steps of a wave in a slab
         const int lane = tid & 63, w = tid >> 6, wk = uni(w / (WM * WN)), wm = w % (WM * WN) / WN, wn = w % WN;
         unsigned char* const lds = st.template at<0>();
@@ -1286,9 +1374,11 @@ struct Gemm {
                         c = mfma16<DT>(af[i], bf[j], c);
                     }
             }
+            sums.slab(acc);
             free = cur;
             cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
         }
+        sums.finish(acc);
         step_barrier();
         if constexpr (WK > 1) add_waves(lds, acc, wk, lane, std::make_integer_sequence<int, FM>{});
         else step_barrier();
@@ -1336,7 +1426,7 @@ struct Gemm {
     // Slabs of iterations from kedge on get per-chunk edge checks, inside the
     // same pipeline.
     static __device__ __forceinline__ void loop(const Prob& a, const Stages& st, int m0, int n0, int kbeg, int kend,
-                                                int kedge, Acc& acc, int tid) {
+                                                int kedge, bool out32, Acc& acc, int tid) {
         tid = opaque(tid);
         SA sa;
         SB sb;
@@ -1345,8 +1435,10 @@ struct Gemm {
         sb.init(a.B, a.ldb, n0, a.N, kbeg, a.K, tid);
         __syncthreads();   // LDS may still be in use (previous epilogue or loop)
         prologue(a, sa, sb, kbeg, kend, kedge, m0, n0, st, tid, std::make_integer_sequence<int, NS - 1>{});
+        Sums sums;
+        if constexpr (!kBlocks32) sums.start(kend - kbeg, out32);
         if constexpr (kStream) {
-            stream_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, tid);
+            stream_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, sums, tid);
             return;
         }
         wait_slab(min(NS - 2, kend - 1 - kbeg));
@@ -1357,12 +1449,22 @@ struct Gemm {
         step_barrier();
         if constexpr (kStream) {
         } else if constexpr (kSeam) {
-            slab_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, tid);
+            slab_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, sums, tid);
         } else {
+            if constexpr (kBlocks32) {
+                static_assert(NS == 2, "two sets of accumulators");
+                zero(sums.sum);
+                zero(sums.odd);
+            }
             for (int kk = kbeg;; kk += NS)
-                if (!steps(a, sa, sb, kk, kbeg, kend, kedge, m0, n0, st, acc, tid,
+                if (!steps(a, sa, sb, kk, kbeg, kend, kedge, m0, n0, st, acc, sums, tid,
                            std::make_integer_sequence<int, NS>{}))
-                    return;
+                    break;
+            if constexpr (kBlocks32) {
+                // the last slab's sums (of slab kbeg in acc, kbeg + 1 in odd, ...)
+                add(sums.sum, (kend - kbeg) % 2 ? acc : sums.odd);
+                acc = sums.sum;
+            }
         }
     }
 
@@ -1375,21 +1477,8 @@ struct Gemm {
     // 16-byte chunks: chunks past the M or N edge of an MN-contiguous operand
     // only feed rows or columns of the tile that are never written.
     static __device__ __forceinline__ void mac_loop(const Prob& a, const Stages& st, int tile, int klo, int khi,
-                                                    Acc& acc, int tid) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                if constexpr (DT == DT_F64) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) acc.v[i][j][q] = f64x4{0, 0, 0, 0};
-                } else if constexpr (kHalf) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) acc.v[i][j][q] = f32x4{0, 0, 0, 0};
-                } else {
-                    acc.v[i][j] = f32x16{0};
-                }
-            }
+                                                    bool out32, Acc& acc, int tid) {
+        zero(acc);
         if (klo >= khi) return;
         int m0, n0;
         tile_origin(a, tile, m0, n0);
@@ -1399,7 +1488,7 @@ struct Gemm {
         // rows shorter than a chunk: chunks of earlier rows can reach the end too
         const bool check_all = (a_edge && a.lda * EB < 16) || (b_edge && a.ldb * EB < 16);
         const int kedge = check_all ? klo : check_last ? klast : khi;
-        loop(a, st, m0, n0, klo, khi, kedge, acc, tid);
+        loop(a, st, m0, n0, klo, khi, kedge, out32, acc, tid);
     }
 
     // Partial tiles are stored in fragment order: 16-byte chunk q of thread
@@ -1961,7 +2050,7 @@ struct Gemm {
             stamp(ts, 0, tid);
             stamp_clock(ts, 5, tid);
 
-            mac_loop(pr, st, tile, lo, hi, acc, tid);
+            mac_loop(pr, st, tile, lo, hi, a.out_dtype == DT_F32, acc, tid);
             stamp(ts, 1, tid);
 
             constexpr int ALL = (1 << UNITS) - 1;
