@@ -60,6 +60,9 @@ const void* kernel_table(bool akc, bool bkc, int v) {
             case 10: return kc_only<DT, 10, FULL>(akc, bkc);   // streaming tiles
             case 11: return kc_only<DT, 11, FULL>(akc, bkc);
             case 12: return any_layout<DT, 12, FULL>(akc, bkc);  // quarter-size tile
+            case 13: return kc_only<DT, 13, FULL>(akc, bkc);   // 10 to 12 for FP32 results
+            case 14: return kc_only<DT, 14, FULL>(akc, bkc);
+            case 15: return any_layout<DT, 15, FULL>(akc, bkc);
             default: return nullptr;
         }
     } else if constexpr (DT == DT_F8) {

@@ -138,6 +138,14 @@ template <> struct Cfg<DT_F16, 11> { static constexpr int EB = 2, BM = kTile16R6
 template <> struct Cfg<DT_BF16, 10> : Cfg<DT_F16, 10> {};
 template <> struct Cfg<DT_BF16, 11> : Cfg<DT_F16, 11> {};
 
+// The streaming and quarter-size tiles with sums in blocks, for FP32 results.
+template <> struct Cfg<DT_F16, 13> : Cfg<DT_F16, 10> {};
+template <> struct Cfg<DT_F16, 14> : Cfg<DT_F16, 11> {};
+template <> struct Cfg<DT_F16, 15> : Cfg<DT_F16, 12> {};
+template <> struct Cfg<DT_BF16, 13> : Cfg<DT_F16, 10> {};
+template <> struct Cfg<DT_BF16, 14> : Cfg<DT_F16, 11> {};
+template <> struct Cfg<DT_BF16, 15> : Cfg<DT_F16, 12> {};
+
 // Optional tile traits: WPE overrides the waves per SIMD the register budget
 // is sized for.
 template <class C, class = void> struct ConvOf { static constexpr bool value = false; };
@@ -766,22 +774,28 @@ struct Gemm {
     // 384x384x1024 1.9e-7 / 2.3e-7 / 1.2e-7.  The FP32 tile's launches take 2-6 %
     // longer for it (504x376x136 9.0 us against 8.5), the others' do not.
     static constexpr bool kBlocks32 = DT == DT_F32 && V == 1;
-    static constexpr bool kBlocks16 = kHalf && (V == kVariantQuarter || WK > 1);
+    static constexpr bool kBlocks16 = kHalf && V > kVariantQuarter;
     // FP32: a block is a slab, 16 MFMAs.  The slabs take turns between two sets of
     // accumulators, so that one is added up behind the other's MFMAs.
     struct Turns {
         Acc sum, odd;
+
+        __device__ __forceinline__ explicit Turns(int) {
+            zero(sum);
+            zero(odd);
+        }
     };
     // 16-bit types: two MFMAs a slab, blocks of sqrt(slabs / 2) slabs.  A 16-bit
-    // result's own rounding hides the sum's, so only FP32 results ask for them.
+    // result's own rounding hides the sum's (its error is the same to four digits), so
+    // only kernels with an FP32 result have them: in one kernel for both, the second
+    // form's registers cost the first 2-7 % (539x217x1167 9.5 us, 10.2).
     struct Blocks {
         Acc sum;
         int block, left;           // slabs in a block, and until the next one
 
-        __device__ __forceinline__ void start(int slabs, bool on) {
+        __device__ __forceinline__ explicit Blocks(int slabs) {
             zero(sum);
-            block = on ? max(1, uni(int(__builtin_sqrtf(0.5f * float(slabs)) + 0.5f))) : slabs + 1;
-            left = block;
+            block = left = max(1, uni(int(__builtin_sqrtf(0.5f * float(slabs)) + 0.5f)));
         }
         __device__ __forceinline__ void slab(Acc& acc) {
             if (--left) return;
@@ -795,7 +809,7 @@ struct Gemm {
         }
     };
     struct NoSums {
-        __device__ __forceinline__ void start(int, bool) {}
+        __device__ __forceinline__ explicit NoSums(int) {}
         __device__ __forceinline__ void slab(Acc&) {}
         __device__ __forceinline__ void finish(Acc&) {}
     };
@@ -882,8 +896,9 @@ struct Gemm {
     }
 
     // MFMAs over one staged k-slab.
+    template <class Behind>
     static __device__ __forceinline__ void compute(const unsigned char* As, const unsigned char* Bs,
-                                                   Acc& acc, int wm, int wn, int lane) {
+                                                   Acc& acc, int wm, int wn, int lane, Behind&& behind) {
         const int g = lane >> 5, l32 = lane & 31;
         static_assert(!kSeam, "16-bit types and FP8 run slab_loop");
         if constexpr (DT == DT_F64) {
@@ -980,6 +995,8 @@ struct Gemm {
 #pragma unroll
                 for (int i = 1; i < FM; ++i) read_a(i);
                 if constexpr (AKC && BKC) __builtin_amdgcn_sched_barrier(0);
+                // while the fragments come in and the first MFMAs run
+                if (c == 1) behind();
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -1052,10 +1069,13 @@ struct Gemm {
         if constexpr (kBlocks32) {
             Acc &mine = U ? sums.odd : acc, &last = U ? acc : sums.odd;
             zero(mine);
-            compute(cur, cur + SA::BYTES, mine, wm, wn, lane);
-            add(sums.sum, last);
+            compute(cur, cur + SA::BYTES, mine, wm, wn, lane, [&] {
+                __builtin_amdgcn_sched_barrier(0);
+                add(sums.sum, last);
+                __builtin_amdgcn_sched_barrier(0);
+            });
         } else {
-            compute(cur, cur + SA::BYTES, acc, wm, wn, lane);
+            compute(cur, cur + SA::BYTES, acc, wm, wn, lane, [] {});
         }
         const bool more = it + 1 < kend;
         if (more) {
@@ -1426,7 +1446,7 @@ struct Gemm {
     // Slabs of iterations from kedge on get per-chunk edge checks, inside the
     // same pipeline.
     static __device__ __forceinline__ void loop(const Prob& a, const Stages& st, int m0, int n0, int kbeg, int kend,
-                                                int kedge, bool out32, Acc& acc, int tid) {
+                                                int kedge, Acc& acc, int tid) {
         tid = opaque(tid);
         SA sa;
         SB sb;
@@ -1435,9 +1455,8 @@ struct Gemm {
         sb.init(a.B, a.ldb, n0, a.N, kbeg, a.K, tid);
         __syncthreads();   // LDS may still be in use (previous epilogue or loop)
         prologue(a, sa, sb, kbeg, kend, kedge, m0, n0, st, tid, std::make_integer_sequence<int, NS - 1>{});
-        Sums sums;
-        if constexpr (!kBlocks32) sums.start(kend - kbeg, out32);
         if constexpr (kStream) {
+            Sums sums(kend - kbeg);
             stream_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, sums, tid);
             return;
         }
@@ -1449,13 +1468,11 @@ struct Gemm {
         step_barrier();
         if constexpr (kStream) {
         } else if constexpr (kSeam) {
+            Sums sums(kend - kbeg);
             slab_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, sums, tid);
         } else {
-            if constexpr (kBlocks32) {
-                static_assert(NS == 2, "two sets of accumulators");
-                zero(sums.sum);
-                zero(sums.odd);
-            }
+            Sums sums(kend - kbeg);
+            static_assert(!kBlocks32 || NS == 2, "two sets of accumulators");
             for (int kk = kbeg;; kk += NS)
                 if (!steps(a, sa, sb, kk, kbeg, kend, kedge, m0, n0, st, acc, sums, tid,
                            std::make_integer_sequence<int, NS>{}))
@@ -1477,7 +1494,7 @@ struct Gemm {
     // 16-byte chunks: chunks past the M or N edge of an MN-contiguous operand
     // only feed rows or columns of the tile that are never written.
     static __device__ __forceinline__ void mac_loop(const Prob& a, const Stages& st, int tile, int klo, int khi,
-                                                    bool out32, Acc& acc, int tid) {
+                                                    Acc& acc, int tid) {
         zero(acc);
         if (klo >= khi) return;
         int m0, n0;
@@ -1488,7 +1505,7 @@ struct Gemm {
         // rows shorter than a chunk: chunks of earlier rows can reach the end too
         const bool check_all = (a_edge && a.lda * EB < 16) || (b_edge && a.ldb * EB < 16);
         const int kedge = check_all ? klo : check_last ? klast : khi;
-        loop(a, st, m0, n0, klo, khi, kedge, out32, acc, tid);
+        loop(a, st, m0, n0, klo, khi, kedge, acc, tid);
     }
 
     // Partial tiles are stored in fragment order: 16-byte chunk q of thread
@@ -2050,7 +2067,7 @@ struct Gemm {
             stamp(ts, 0, tid);
             stamp_clock(ts, 5, tid);
 
-            mac_loop(pr, st, tile, lo, hi, a.out_dtype == DT_F32, acc, tid);
+            mac_loop(pr, st, tile, lo, hi, acc, tid);
             stamp(ts, 1, tid);
 
             constexpr int ALL = (1 << UNITS) - 1;
