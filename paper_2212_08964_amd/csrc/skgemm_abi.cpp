@@ -140,7 +140,7 @@ void model_for(int dt, int v, double* m) {
     if (dt == DT_F64) { m[0] = 5.00; m[1] = 1.23; m[2] = 0.713; m[3] = 1.13; m[4] = 2.09; return; }
     // the quarter-size tiles: fits over 1-256 (fp32: 1-1024) workgroups, 1-8 shares a tile
     if (v == kVariantQuarter) { m[0] = 4.73; m[1] = 1.37; m[2] = 0.243; m[3] = 0.525; m[4] = 0.505; return; }
-    if (dt == DT_F32 && v == 1) { m[0] = 4.55; m[1] = 1.37; m[2] = 0.762; m[3] = 0.585; m[4] = 2.450; return; }
+    if (dt == DT_F32 && v == 1) { m[0] = 4.55; m[1] = 1.37; m[2] = 0.807; m[3] = 0.585; m[4] = 2.580; return; }
     if (dt == DT_F32) { m[0] = 6.20; m[1] = 1.25; m[2] = 2.07; m[3] = 0.569; m[4] = 3.99; return; }
     // the convolution variants take the constants of the GEMM tile of their shape
     // the three-stage small tile: calibrate.py's grid mode with e from one
@@ -717,6 +717,13 @@ static bool quarter_fits(const skgemm_plan_s* base, int v, const skgemm_options_
     return t <= cus || (t <= 2 * int64_t(cus) && cdiv(K[0], kTile16Q.bk) <= 16);
 }
 
+// Whether the rows of both operands, as the caller is expected to pass them
+// (leading dimension = row length), all start on multiples of `bytes`.
+static bool rows_start_on(const skgemm_plan_s* pl, int bytes) {
+    const int eb = elem_bytes(pl->ta);
+    return (pl->akc ? pl->K : int64_t(pl->Ml)) * eb % bytes == 0 && (pl->bkc ? pl->K : int64_t(pl->Nl)) * eb % bytes == 0;
+}
+
 // Builds the plan for every admissible tile variant (the one the options
 // name, else all that exist) and keeps the one with the smallest modelled
 // runtime (the default tile on ties); the small 16-bit tile competes on its
@@ -761,8 +768,11 @@ static skgemm_status_t plan_variants(skgemm_plan_s* base, const skgemm_options_t
         // at most two workgroups per CU (three: 960x832x3456, 195 tiles on 585, 18.1 us
         // against 17.4 on the 128x128 tile; 24 of 484x103x1113, 384 on 768, 19.5
         // against 18.2),
-        // and over more than one only up to 64 slabs a tile (2145x158x5418, 102 on
-        // 510, 85 slabs: 21.8 against 21.1; 1920x320x2944, 46: 13.9 against 16.4).
+        // and over more than one only up to so many slabs a tile: 64 where the rows of
+        // both operands start on 128-byte lines, 32 where on 16 bytes, else 24 (of 430
+        // such splits, share of the other tiles' time, mean and most: within the limits
+        // 0.89 and 1.01, 0.89 and 0.97, 0.95 and 1.02; beyond the last two 0.96 and 1.20,
+        // 1.04 and 1.29: 1647x457x3961, 208 tiles on 416, 62 slabs, 28.3 us against 21.9).
         if (pl && v == kVariantQuarter && !named && pl->g_sk > 0 && pl->occ > 0) {
             const int64_t cus = pl->p / pl->occ;
             skgemm_options_t oq = o;
@@ -773,7 +783,8 @@ static skgemm_status_t plan_variants(skgemm_plan_s* base, const skgemm_options_t
                 delete pl;
                 pl = build_variant(base, v, oq, G, M, N, K, &st);
             }
-            if (pl && pl->g_sk > 0 && pl->grid > cus && pl->ipt > 64) {
+            if (pl && pl->g_sk > 0 && pl->grid > cus &&
+                pl->ipt > (rows_start_on(pl, 128) ? 64 : rows_start_on(pl, 16) ? 32 : 24)) {
                 delete pl;
                 continue;
             }
@@ -781,10 +792,14 @@ static skgemm_status_t plan_variants(skgemm_plan_s* base, const skgemm_options_t
         // The FP32 one splits up to a tile and a half per CU, a third from 160 slabs a
         // tile on (768x2304x768, 432 tiles, 34.4 us against 34.0 on the 128x128
         // tile; 510x859x5621, 112 of 176 slabs, 56.0 against 53.3; 192x1728x7104,
-        // 81 of 222, 52.9 against 63.4).
+        // 81 of 222, 52.9 against 63.4), and with more than 64 slabs not over more than
+        // three workgroups per CU, but where an eighth of the 128x128 tiles is padding (0.84-1.02
+        // of their time, elsewhere 0.97-1.09: 512x2048x4416, 256 tiles on 1024, 87.9 us
+        // against 81.2 on 256).
         if (pl && !named && base->dtype == DT_F32 && v == 1 && pl->g_sk > 0 && pl->occ > 0) {
             const int64_t cus = pl->p / pl->occ;
-            if (2 * int64_t(pl->t) > 3 * cus || (pl->ipt >= 160 && 3 * int64_t(pl->t) > cus)) {
+            if (2 * int64_t(pl->t) > 3 * cus || (pl->ipt >= 160 && 3 * int64_t(pl->t) > cus) ||
+                (pl->ipt > 64 && pl->grid > 3 * cus && cand[0] && 2 * int64_t(pl->t) > 7 * int64_t(cand[0]->t))) {
                 delete pl;
                 continue;
             }

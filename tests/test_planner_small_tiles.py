@@ -1,0 +1,53 @@
+"""Where automatic plans take the small tiles (64x64 and 32x256), on 256 CUs with the
+co-residencies of the device: shapes on both sides of each limit, each measured on
+both tiles.  Times in us, small tile / the other."""
+import pytest
+
+from paper_2212_08964_amd import skgemm as s
+
+QUARTER16, QUARTER32 = (64, 64, 64), (64, 64, 32)
+
+
+def info(M, N, K, la=0, lb=0, ta=s.BF16, occupancy=3, tile=None, batch=0):
+    kw = dict(ta=ta, num_cus=256, occupancy=occupancy, tile=tile)
+    return (s.BatchedPlan(batch, M, N, K, la, lb, **kw) if batch else s.Plan(M, N, K, la, lb, **kw)).info()
+
+
+@pytest.mark.parametrize("M,N,K,la,lb,quarter", [
+    (1647, 457, 3961, 0, 0, False),      # rows off 16 bytes, 62 slabs: 28.3 / 21.9
+    (2413, 351, 3327, 0, 0, False),      # 52: 25.4 / 21.0
+    (256, 4096, 2802, 0, 1, False),      # 44: 21.0 / 18.8
+    (640, 1392, 3688, 0, 1, False),      # rows on 16 bytes, 58: 22.9 / 19.1
+    (2539, 265, 3032, 0, 1, False),      # 48: 19.9 / 18.1
+    (1920, 320, 2944, 0, 0, True),       # rows on 128 bytes, 46: 13.9 / 16.4
+    (1792, 384, 3584, 0, 1, True),       # 56: 14.9 / 17.6
+    (576, 896, 4032, 0, 0, True),        # 63: 15.2 / 18.1
+    (1400, 472, 2040, 0, 1, True),       # rows on 16 bytes, 32 slabs
+    (1024, 1024, 1024, 0, 0, True),      # one workgroup per CU
+])
+def test_quarter_split_limits(M, N, K, la, lb, quarter):
+    assert (info(M, N, K, la, lb)["tile"][:3] == QUARTER16) == quarter
+
+
+def test_quarter_split_over_two_per_cu():
+    """A split the model would spread over more than two workgroups per CU keeps to
+    two, in whole shares a tile; with one share it is data-parallel."""
+    i = info(960, 832, 3456)
+    assert i["tile"][:3] == QUARTER16 and i["t"] == 195 and i["grid"] == i["g_sk"] == 390
+    for M, N, K in [(1856, 320, 1984), (768, 768, 1600), (832, 832, 2048), (1408, 384, 1536)]:
+        i = info(M, N, K)
+        assert i["tile"][:3] == QUARTER16 and i["grid"] <= 512 and i["g_sk"] % i["t"] == 0, (M, N, K)
+    # named, the tile keeps the model's own split
+    assert info(960, 832, 3456, tile=QUARTER16)["grid"] > 512
+    assert info(2145, 158, 5418)["tile"][:3] != QUARTER16           # 85 slabs
+
+
+@pytest.mark.parametrize("M,N,K,la,lb,quarter", [
+    (384, 384, 1024, 0, 0, True), (300, 500, 2000, 0, 0, True),
+    (510, 859, 5621, 0, 0, False),       # 176 slabs over a third of the CUs: 56.0 / 53.3
+    (768, 2304, 768, 0, 0, False),       # more than a tile and a half per CU: 34.4 / 34.0
+    (512, 2048, 4416, 1, 0, False),      # 1024 workgroups of 138 slabs: 87.9 / 81.2
+    (369, 2405, 3279, 1, 0, False),      # 912 of 103: 68.4 / 63.4
+])
+def test_quarter_fp32_limits(M, N, K, la, lb, quarter):
+    assert (info(M, N, K, la, lb, ta=s.F32, occupancy=4)["tile"][:3] == QUARTER32) == quarter
