@@ -1,6 +1,7 @@
-"""Where automatic plans take the small tiles (64x64 and 32x256), on 256 CUs with the
-co-residencies of the device: shapes on both sides of each limit, each measured on
-both tiles.  Times in us, small tile / the other."""
+"""Where automatic plans take the small tiles (64x64 and 32x256): shapes on both
+sides of each limit, measured on both tiles (times in us, small tile / the other).
+A plan without a GPU has one co-residency for every tile, so the limits that weigh
+tiles against each other are checked with the device's own."""
 import pytest
 
 from paper_2212_08964_amd import skgemm as s
@@ -8,11 +9,15 @@ from paper_2212_08964_amd import skgemm as s
 QUARTER16, QUARTER32 = (64, 64, 64), (64, 64, 32)
 
 
-def info(M, N, K, la=0, lb=0, ta=s.BF16, occupancy=3, tile=None, batch=0):
-    kw = dict(ta=ta, num_cus=256, occupancy=occupancy, tile=tile)
-    return (s.BatchedPlan(batch, M, N, K, la, lb, **kw) if batch else s.Plan(M, N, K, la, lb, **kw)).info()
+def info(M, N, K, la=0, lb=0, ta=s.BF16, num_cus=256, occupancy=3, tile=None):
+    return s.Plan(M, N, K, la, lb, ta=ta, num_cus=num_cus, occupancy=occupancy, tile=tile).info()
 
 
+def on_device(*args, **kw):
+    return info(*args, num_cus=0, occupancy=0, **kw)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K,la,lb,quarter", [
     (1647, 457, 3961, 0, 0, False),      # rows off 16 bytes, 62 slabs: 28.3 / 21.9
     (2413, 351, 3327, 0, 0, False),      # 52: 25.4 / 21.0
@@ -26,7 +31,7 @@ def info(M, N, K, la=0, lb=0, ta=s.BF16, occupancy=3, tile=None, batch=0):
     (1024, 1024, 1024, 0, 0, True),      # one workgroup per CU
 ])
 def test_quarter_split_limits(M, N, K, la, lb, quarter):
-    assert (info(M, N, K, la, lb)["tile"][:3] == QUARTER16) == quarter
+    assert (on_device(M, N, K, la, lb)["tile"][:3] == QUARTER16) == quarter
 
 
 def test_quarter_split_over_two_per_cu():
@@ -37,17 +42,20 @@ def test_quarter_split_over_two_per_cu():
     for M, N, K in [(1856, 320, 1984), (768, 768, 1600), (832, 832, 2048), (1408, 384, 1536)]:
         i = info(M, N, K)
         assert i["tile"][:3] == QUARTER16 and i["grid"] <= 512 and i["g_sk"] % i["t"] == 0, (M, N, K)
+    assert info(1647, 457, 3961)["tile"][:3] != QUARTER16 != info(256, 4096, 2802, 0, 1)["tile"][:3]
     # named, the tile keeps the model's own split
     assert info(960, 832, 3456, tile=QUARTER16)["grid"] > 512
     assert info(2145, 158, 5418)["tile"][:3] != QUARTER16           # 85 slabs
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K,la,lb,quarter", [
     (384, 384, 1024, 0, 0, True), (300, 500, 2000, 0, 0, True),
     (510, 859, 5621, 0, 0, False),       # 176 slabs over a third of the CUs: 56.0 / 53.3
     (768, 2304, 768, 0, 0, False),       # more than a tile and a half per CU: 34.4 / 34.0
     (512, 2048, 4416, 1, 0, False),      # 1024 workgroups of 138 slabs: 87.9 / 81.2
     (369, 2405, 3279, 1, 0, False),      # 912 of 103: 68.4 / 63.4
+    (3008, 192, 3840, 1, 1, True),       # a quarter of the 128x128 tiles is padding: 47.5 / 60.8
 ])
 def test_quarter_fp32_limits(M, N, K, la, lb, quarter):
-    assert (info(M, N, K, la, lb, ta=s.F32, occupancy=4)["tile"][:3] == QUARTER32) == quarter
+    assert (on_device(M, N, K, la, lb, ta=s.F32)["tile"][:3] == QUARTER32) == quarter
