@@ -653,18 +653,41 @@ static skgemm_plan_s* build_variant(const skgemm_plan_s* base, int v, const skge
     return pl;
 }
 
+// Whether a product of at most 32 rows with t streaming tiles of ipt slabs, more
+// than one tile per CU, takes them.  A second wave costs the streaming tile what
+// the 64x256 tile, split over the CUs in one wave, does not have; what it gains is
+// the longer runs, worth the more the longer k is.  Measured over 990 shapes of
+// 8200 to 60000 columns, 300 to 16000 k, streaming tile / best other:
+//  * more than 32 slabs: 0.60-1.0 whatever the tiles;
+//  * 25 to 32: 0.63-0.95 above three waves and where the last one is two fifths full;
+//    below, 0.94-1.10;
+//  * 17 to 24: 0.70-0.96 between four and eight waves and where the last one is four
+//    fifths full (128256x5120, sixteen waves, 1.11); else up to 1.24;
+//  * fewer: 1.03-2.1 above two waves and a little (32000x4096, 1000 tiles, 49.3 us
+//    against 44.7; 50304x2048, 50.2 against 32.6).  Up to there, a remainder of an
+//    eighth included, which is split: 0.90-1.08 where rows start on 8 bytes, up to
+//    1.31 elsewhere; not for a short last wave of short tiles (13x10715x1152, 335
+//    tiles of 5 slabs, 16.1 us against 12.8) nor for short tiles whose last slab is
+//    mostly padding (k padded by a twentieth: 24x17000x2176, 30.2 against 27.5).
+static bool stream_waves(int64_t t, int64_t ipt, int64_t k, int64_t cus, int eb) {
+    const int64_t rem = t % cus, last = rem ? rem : cus;
+    if (ipt > 32) return true;
+    if (ipt > 24 && (t > 3 * cus || 5 * last >= 2 * cus)) return true;
+    if (ipt > 16 && (t > 4 * cus ? t <= 8 * cus : 5 * last >= 4 * cus)) return true;
+    return 8 * t <= 17 * cus && k * eb % 8 == 0 && !(ipt < 8 && 5 * rem < 3 * cus && rem) &&
+           !(ipt < 12 && 20 * (ipt * kTile16R32.bk - k) >= k);
+}
+
 // The streaming tile an automatic plan of a single GEMM with both operands
 // K-contiguous takes, or -1.  At most 32 rows (measured over 1 to 32 rows, 1024
 // to 16384 columns and 1024 to 8192 k, odd sizes among them: 1.2-1.7x the best
-// of the other tiles up to one tile per CU, 0.98-1.27x above): always, but for
-// a short last wave of short tiles (13x10715x1152, 335 tiles of 5 slabs: 16.1
-// us against 12.8; 16x20000x333, 625 of 2: 20.3 against 10.2), and for short
-// tiles above one per CU whose last slab is mostly padding (k padded by a
-// twentieth: 24x17000x2176, 30.2 against 27.5; 1x8700x2176, 17.5 against 16.7).  33
-// to 64 rows: where its tiles fit the CUs in one wave and the rows of both
-// operands start on 128-byte lines (1.0-1.32x); with more tiles, or every run of
-// a slab across a line more, its half of A a slab costs more than the longer
-// runs gain (64x11000x5000 40.7 us on the 64x256 tile, 50.2 here).
+// of the other tiles up to one tile per CU): always up to one tile per CU, above
+// by stream_waves.  33 to 64 rows: where its tiles fit the CUs in one wave and the
+// rows of both operands start on 128-byte lines (1.0-1.32x); with more tiles, or
+// every run of a slab across a line more, its half of A a slab costs more than the
+// longer runs gain (64x11000x5000 40.7 us on the 64x256 tile, 50.2 here), and with
+// more than 32 slabs the few workgroups take longer than shares over all CUs
+// (49x5120x11840, 160 tiles of 47 slabs, 40.2 us against 33.0).
 static int stream_variant(const skgemm_plan_s* base, const skgemm_options_t& o, const int64_t* M, const int64_t* N,
                           const int64_t* K) {
     if (base->G || base->conv || base->batch != 1 || !base->akc || !base->bkc || o.policy != SKGEMM_POLICY_AUTO ||
@@ -677,10 +700,8 @@ static int stream_variant(const skgemm_plan_s* base, const skgemm_options_t& o, 
     if (v < 0 || !kernel_exists(base->dtype, true, true, v)) return -1;
     int cus = o.num_cus, occ = 1;
     if (!cus && device_capacity(base->dtype, true, true, v, &cus, &occ) != SKGEMM_OK) return -1;
-    const int64_t t = cdiv(cols, kTile16R32.bn), rem = t % cus, ipt = cdiv(K[0], kTile16R32.bk);
-    if (t > cus && (v == kVariantStream64 || (ipt < 8 && 5 * rem < 3 * cus && rem) ||
-                    (ipt < 12 && 20 * (ipt * kTile16R32.bk - K[0]) >= K[0])))
-        return -1;
+    const int64_t t = cdiv(cols, kTile16R32.bn), ipt = cdiv(K[0], kTile16R32.bk);
+    if (v == kVariantStream64 ? t > cus || ipt > 32 : t > cus && !stream_waves(t, ipt, K[0], cus, elem_bytes(base->ta))) return -1;
     return v;
 }
 

@@ -59,3 +59,32 @@ def test_quarter_split_over_two_per_cu():
 ])
 def test_quarter_fp32_limits(M, N, K, la, lb, quarter):
     assert (on_device(M, N, K, la, lb, ta=s.F32)["tile"][:3] == QUARTER32) == quarter
+
+
+@pytest.mark.parametrize("M,N,K,stream", [
+    (1, 32000, 4096, False),      # 1000 tiles of 16 slabs: 49.3 / 45.4
+    (16, 50304, 2048, False),     # 1572 of 8: 51.2 / 33.2
+    (16, 128256, 5120, False),    # 4008 of 20, sixteen waves: 262.8 / 218.7
+    (1, 28672, 3072, False),      # 896 of 12: 36.9 / 32.3
+    (22, 17088, 4991, False),     # 534 of 20, a short third wave: 1.17x
+    (3, 17280, 6403, False),      # 540 of 26, the same: 1.10x
+    (1, 9249, 1214, False),       # rows off 8 bytes
+    (1, 50304, 8192, True),       # 32 slabs, seven waves: 151.6 / 189.7
+    (16, 128256, 8192, True),     # sixteen: 348.6 / 407.0
+    (1, 32000, 5120, True),       # 20 slabs, last wave nearly full: 60.4 / 67.3
+    (1, 50304, 5120, True),       # seven waves: 107.2 / 115.3
+    (1, 16384, 4096, True),       # two full waves: 25.7 / 26.4
+    (4, 9983, 9984, True),        # more than 32 slabs
+    (16, 8192, 300, True),        # one wave
+])
+def test_streaming_waves(M, N, K, stream):
+    """Above one streaming tile per CU the number of slabs and the fill of the last
+    wave decide."""
+    i = info(M, N, K, 0, 1, occupancy=2)
+    assert (i["tile"][:3] == (32, 32, 256)) == stream
+
+
+@pytest.mark.parametrize("K,stream", [(4096, True), (8192, True), (8256, False), (11840, False)])
+def test_streaming_64_rows(K, stream):
+    """33 to 64 rows: up to 32 slabs (49x5120x11840: 40.2 / 33.0)."""
+    assert (info(49, 5120, K, 0, 1, occupancy=2)["tile"][:3] == (64, 32, 256)) == stream
