@@ -25,12 +25,14 @@ int kernel_threads_f64(int v);
 enum Form {
     FORM_FULL = 1,       // with the group table, batch, trace and timestamp paths
     FORM_OUT32 = 2,      // for FP32 results
-    FORMS = 4
+    FORM_RAGGED = 4,     // for operands whose rows do not start on 16 bytes
+    FORMS = 8
 };
 
 static const void* kernel_for(int dtype, bool akc, bool bkc, int v, int form) {
     const bool half = dtype == DT_F16 || dtype == DT_BF16, full = form & FORM_FULL;
     if (half && (form & FORM_OUT32)) v = with_block_sums(v);
+    if ((form & FORM_RAGGED) && ((half && v == 2) || (dtype == DT_F8 && v == 1))) v = kKernelRagged;
     switch (dtype) {
         case DT_F32: return full ? kernel_fn_f32_full(akc, bkc, v) : kernel_fn_f32(akc, bkc, v);
         case DT_F16: return full ? kernel_fn_f16_full(akc, bkc, v) : kernel_fn_f16(akc, bkc, v);
@@ -42,6 +44,20 @@ static const void* kernel_for(int dtype, bool akc, bool bkc, int v, int form) {
 }
 
 static bool needs_full(const KArgs& a) { return a.G || a.batch > 1 || a.trace || a.times; }
+
+// The FP8 tile where either operand's rows start off 16 bytes.  The 16-bit one
+// where B's do (A's alone: 2176x2048x2047 37.8 us on the seam loop, 40.5 without)
+// and a workgroup runs more than 16 slabs of a tile: of 230 ragged launches the seam
+// loop's time goes to 0.97 (0.90-1.05) there, to 1.02 (0.96-1.11) with fewer.
+static bool ragged(int dtype, const KArgs& a) {
+    if (a.G) return false;              // the table's operands are not known here
+    if (dtype != DT_F8 && (a.t > a.sk_tiles ? a.ipt : a.sk_q) <= 16) return false;
+    const int eb = dtype == DT_F8 ? 1 : 2;
+    const auto off = [&](const void* x, int64_t ld, int64_t stride) {
+        return ((reinterpret_cast<uintptr_t>(x) | uint64_t(ld * eb) | uint64_t(a.batch > 1 ? stride : 0)) & 15) != 0;
+    };
+    return off(a.B, a.ldb, a.stride_b) || (dtype == DT_F8 && off(a.A, a.lda, a.stride_a));
+}
 
 bool kernel_exists(int dtype, bool akc, bool bkc, int v) {
     for (int form = 0; form < FORMS; ++form)
@@ -75,7 +91,8 @@ int kernel_occupancy(int dtype, bool akc, bool bkc, int v) {
 }
 
 int launch_gemm(int dtype, bool akc, bool bkc, int v, const KArgs& args, int grid, void* stream) {
-    const int form = (needs_full(args) ? FORM_FULL : 0) | (args.out_dtype == DT_F32 ? FORM_OUT32 : 0);
+    const int form = (needs_full(args) ? FORM_FULL : 0) | (args.out_dtype == DT_F32 ? FORM_OUT32 : 0) |
+                     (ragged(dtype, args) ? FORM_RAGGED : 0);
     const void* f = kernel_for(dtype, akc, bkc, v, form);
     if (!f) return int(hipErrorInvalidDeviceFunction);
     KArgs copy = args;

@@ -121,13 +121,15 @@ struct KArgs {
 // 9: the same with the convolution gather, substituted for variant 4.
 // 10 and 11: the streaming tiles of 32 and 64 rows (both operands K-contiguous).
 // 12: the quarter-size 64x64 16-bit tile.  The launch takes 13 to 15, the same with
-// sums in blocks, for 10 to 12 with an FP32 result (variants of the kernels, not of plans).
+// sums in blocks, for 10 to 12 with an FP32 result (variants of the kernels, not of plans), and 16 for the 16-bit variant 2 and the FP8
+// variant 1 where operands' rows do not start on 16 bytes.
 constexpr int kVariants = 13;
 constexpr int kVariantDeep = 8;
 constexpr int kVariantDeepConv = 9;
 constexpr int kVariantQuarter = 12;
 constexpr int kVariantStream32 = 10;
 constexpr int kVariantStream64 = 11;
+constexpr int kKernelRagged = 16;
 constexpr int with_block_sums(int v) { return v >= kVariantStream32 && v <= kVariantQuarter ? v + 3 : v; }
 constexpr bool is_stream_variant(int v) { return v == kVariantStream32 || v == kVariantStream64; }
 constexpr bool is_quarter_variant(int dt, int v) { return v == kVariantQuarter || (dt == DT_F32 && v == 1); }

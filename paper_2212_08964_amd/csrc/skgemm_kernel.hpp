@@ -146,6 +146,17 @@ template <> struct Cfg<DT_BF16, 13> : Cfg<DT_F16, 10> {};
 template <> struct Cfg<DT_BF16, 14> : Cfg<DT_F16, 11> {};
 template <> struct Cfg<DT_BF16, 15> : Cfg<DT_F16, 12> {};
 
+// The eight-wave 128x128 16-bit tile and the small FP8 tile for operands whose
+// rows do not start on 16 bytes.  Such rows' loads keep the memory pipeline busy
+// two to three times as long, and with two workgroups on a CU the seam loop's
+// workgroups wait for them in step.  Bound by that pipeline, these kernels load a
+// slab in one burst and do not read ahead over the seam: 895x2709x5051 49.3 us on
+// the seam loop, 45.5 here; 3810x632x7775 75.5 and 71.3; FP8 558x3457x4994 31.0 and
+// 29.3.  With rows on 16 bytes the seam loop is 2-20 % faster.
+template <> struct Cfg<DT_F16, 16> : Cfg<DT_F16, 2> { static constexpr int WPE = 4; };
+template <> struct Cfg<DT_BF16, 16> : Cfg<DT_BF16, 2> { static constexpr int WPE = 4; };
+template <> struct Cfg<DT_F8, 16> : Cfg<DT_F8, 1> {};
+
 // Optional tile traits: WPE overrides the waves per SIMD the register budget
 // is sized for.
 template <class C, class = void> struct ConvOf { static constexpr bool value = false; };
@@ -728,7 +739,8 @@ struct Gemm {
     // or four 16x16 ones (16-bit types and FP64; q = 2 * row half + column
     // half), so bands and blocks cover the same rows and columns for every type.
     static constexpr bool kHalf = DT == DT_BF16 || DT == DT_F16;
-    static constexpr bool kSeam = kHalf || DT == DT_F8;      // MAC loop: slab_loop (else step)
+    static constexpr bool kRagged = V == kKernelRagged;
+    static constexpr bool kSeam = kHalf || (DT == DT_F8 && !kRagged);   // MAC loop: slab_loop (else step)
     struct Acc32 { f32x16 v[FM][FN]; };
     struct Acc16 { f32x4 v[FM][FN][4]; };
     struct Acc64 { f64x4 v[FM][FN][4]; };
@@ -774,7 +786,7 @@ struct Gemm {
     // 384x384x1024 1.9e-7 / 2.3e-7 / 1.2e-7.  The FP32 tile's launches take 2-6 %
     // longer for it (504x376x136 9.0 us against 8.5), the others' do not.
     static constexpr bool kBlocks32 = DT == DT_F32 && V == 1;
-    static constexpr bool kBlocks16 = kHalf && V > kVariantQuarter;
+    static constexpr bool kBlocks16 = kHalf && V > kVariantQuarter && V < kKernelRagged;
     // FP32: a block is a slab, 16 MFMAs.  The slabs take turns between two sets of
     // accumulators, so that one is added up behind the other's MFMAs.
     struct Turns {
@@ -900,7 +912,7 @@ struct Gemm {
     static __device__ __forceinline__ void compute(const unsigned char* As, const unsigned char* Bs,
                                                    Acc& acc, int wm, int wn, int lane, Behind&& behind) {
         const int g = lane >> 5, l32 = lane & 31;
-        static_assert(!kSeam, "16-bit types and FP8 run slab_loop");
+        static_assert(!kSeam, "16-bit types and most of FP8 run slab_loop");
         if constexpr (DT == DT_F64) {
             // v_mfma_f64_16x16x4f64: lane l holds A[row l%16][k l/16] and
             // B[k l/16][col l%16] of the k4 step; each 32x32 block is four
@@ -962,6 +974,16 @@ struct Gemm {
                         for (int q = 0; q < 4; ++q)
                             acc.v[i][j][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[i][q >> 1], bf[j][q & 1],
                                                                                  acc.v[i][j][q], 0, 0, 0);
+            }
+        } else if constexpr (DT == DT_F8) {
+            // Lane group g handles k = 64s + 32g .. +31 of step s.  The step's B
+            // fragments, then one A fragment at a time.
+#pragma unroll 1
+            for (int s = 0; s < BK / 64; ++s) {
+                Frags f;
+                read_bs<0, FB>(f, 0, s, Bs, wn, lane);
+                mfma_rows(f, s, As, acc, wm, lane, std::make_integer_sequence<int, FA>{});
+                __builtin_amdgcn_sched_barrier(0);
             }
         } else {
             // Lane group g handles k = 8c + 4g + u of step (c, u).  The first MFMAs need
@@ -1208,7 +1230,7 @@ struct Gemm {
 
     // Slot I of step S; the fragments of the other step are read from the
     // slab at As / Bs.  The scheduling barrier fixes the order.
-    template <int I, int S, bool REFILL>
+    template <int I, int S, bool REFILL, bool READ = true>
     static __device__ __forceinline__ void slot(Frags& f, const unsigned char* As, const unsigned char* Bs, Acc& acc,
                                                 const Refill& rf, const SA& sa, const SB& sb, int wm, int wn,
                                                 int lane) {
@@ -1226,6 +1248,7 @@ struct Gemm {
                 c = mfma16<DT>(f.a[I], f.b[S][j], c);
             }
         }
+        if constexpr (!READ) return;
         // (the fragments read next go into the registers of those just used)
         if constexpr (DT == DT_F8) __builtin_amdgcn_sched_barrier(0);
         if constexpr (S == 0 && I == SPARE) f.spare = read_a<FA - 1>(1, As, wm, lane);
@@ -1242,6 +1265,59 @@ struct Gemm {
                                                      int wn, int lane,
                                                      std::integer_sequence<int, I...>) {
         (slot<I, S, REFILL>(f, As, Bs, acc, rf, sa, sb, wm, wn, lane), ...);
+    }
+
+    // FP8: a step's A fragments in turn against its B fragments.
+    template <int... I>
+    static __device__ __forceinline__ void mfma_rows(const Frags& f, int s, const unsigned char* As, Acc& acc, int wm, int lane,
+                                                     std::integer_sequence<int, I...>) {
+        const auto row = [&](const Frag& a, f32x16 (&c)[FN]) {
+#pragma unroll
+            for (int j = 0; j < FB; ++j)
+                c[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, f.b[0][j], c[j], 0, 0, 0, 127, 0, 127);
+        };
+        (row(read_a<I>(s, As, wm, lane), acc.v[I]), ...);
+    }
+
+    // ---- 16-bit rows that do not start on 16 bytes, two stages: each slab is
+    // loaded in one burst, A first, as soon as the stage is free, and computed
+    // without reads over the seam (see Cfg<., 16>).
+    template <int... I>
+    static __device__ __forceinline__ void second_half(Frags& f, Acc& acc, const Refill& rf, const SA& sa, const SB& sb,
+                                                       int wm, int wn, int lane, std::integer_sequence<int, I...>) {
+        (slot<I, 1, false, false>(f, nullptr, nullptr, acc, rf, sa, sb, wm, wn, lane), ...);
+    }
+    static __device__ __forceinline__ void burst_loop(const Prob& a, SA& sa, SB& sb, int kbeg, int kend, int kedge,
+                                                      int m0, int n0, const Stages& st, Acc& acc, int tid) {
+        static_assert(NS == 2, "two stages");
+        using Slots = std::make_integer_sequence<int, FA>;
+        const int lane = tid & 63, wm = (tid >> 6) / WN, wn = (tid >> 6) % WN;
+        unsigned char* const lds = st.template at<0>();
+        const uint32_t base = lds_addr(lds);
+        Frags f;
+        const Refill rf{};
+        int cur = 0;                       // byte offset of the stage of slab `it`
+        for (int it = kbeg;; ++it) {
+            const int nxt = STAGE - cur;
+            if (it + 1 < kend) {
+                const bool edge = it + 1 >= kedge;
+                issue_a(a, sa, edge, it + 1, m0, base + nxt, tid);
+                issue_b(a, sb, edge, it + 1, n0, base + nxt + SA::BYTES, tid);
+            }
+            read_bs<0, FB>(f, 0, 0, lds + cur + SA::BYTES, wn, lane);
+            read_as(f, 0, lds + cur, wm, lane, Slots{});
+            half_slab<0, false>(f, lds + cur, lds + cur + SA::BYTES, acc, rf, sa, sb, wm, wn, lane, Slots{});
+            second_half(f, acc, rf, sa, sb, wm, wn, lane, Slots{});
+            if (it + 1 >= kend) break;
+            wait_vmem();
+            if (it + 1 >= kedge) {
+                pin(acc);
+                fix_slab(a, sa, sb, it + 1, kbeg, m0, n0, lds + nxt, tid);
+            }
+            step_barrier();
+            cur = nxt;
+        }
+        step_barrier();
     }
 
     // Refill of the stage at `lds` with slab `it`, wholly inside the inner edges.
@@ -1469,7 +1545,8 @@ struct Gemm {
         if constexpr (kStream) {
         } else if constexpr (kSeam) {
             Sums sums(kend - kbeg);
-            slab_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, sums, tid);
+            if constexpr (kRagged) burst_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, tid);
+            else slab_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, sums, tid);
         } else {
             Sums sums(kend - kbeg);
             static_assert(!kBlocks32 || NS == 2, "two sets of accumulators");
