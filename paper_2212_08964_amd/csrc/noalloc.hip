@@ -11,6 +11,7 @@
 // overlap in time on one GPU (two streams) race on it.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <mutex>
 
@@ -63,13 +64,13 @@ extern "C" skgemm_status_t skgemm_run_noalloc(skgemm_plan_t plan, const void* A,
     int64_t info[29] = {};
     skgemm_status_t st = skgemm_plan_info(plan, info, 29);
     if (st != SKGEMM_OK) return st;
-    const size_t need = size_t(info[28]);
-    if (need > kScratchBytes) return SKGEMM_ERR_WORKSPACE;
+    // (what does not fit may still hold the plan's other tile: skgemm_run decides)
+    const size_t need = std::min(size_t(info[28]), kScratchBytes);
     if (need == 0) return skgemm_run(plan, A, lda, B, ldb, C, ldc, alpha, beta, scale_a, scale_b, nullptr, 0, stream);
     void* ws = nullptr;
     st = scratch_ptr(&ws);
     if (st != SKGEMM_OK) return st;
-    const int64_t g_sk = info[13];
+    const int64_t g_sk = need == kScratchBytes ? skg::kMaxFlagLines : info[13];
     // The flags are left at zero by every run that completes its waits; an
     // earlier run whose wait timed out (or that overlapped this one) may have
     // left some raised, so the error word and this plan's flag lines are

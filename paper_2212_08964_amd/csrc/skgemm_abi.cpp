@@ -17,6 +17,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <memory>
 #include <vector>
 
 #include "skgemm.h"
@@ -58,6 +59,10 @@ struct skgemm_plan_s {
     int64_t pack_lines[2], pack_cols[2], pack_ld[2];
     size_t pack_off[2];
     size_t ws_total;                         // ws_bytes plus the re-layout regions
+    // The small FP8 tile's plan where the large tile's was taken for rows off 128
+    // bytes: for calls that only the small tile can run, a leading dimension
+    // whose large slab is beyond 32-bit offsets or a workspace that is too small.
+    std::shared_ptr<skgemm_plan_s> narrow;
     int max_segs;
     // iteration space as problems (a single GEMM is one problem)
     int G;                                  // 0 for a single-GEMM plan
@@ -848,13 +853,20 @@ static skgemm_status_t plan_variants(skgemm_plan_s* base, const skgemm_options_t
     // smallest estimate; between plans the HBM bound makes equal, the smaller
     // compute-model time
     skgemm_plan_s* best = nullptr;
+    std::shared_ptr<skgemm_plan_s> narrow;
     double best_t = 0.0, best_c = 0.0;
     for (skgemm_plan_s* c : cand) {
         if (!c) continue;
         double tc = 0.0;
         double t = plan_estimate(c, &tc);
         if (!named && is_quarter_variant(c->dtype, c->variant)) t /= kQuarterGain;
-        if (!named && small_f8_misaligned(c, o, K)) t *= kSmallF8Misaligned;
+        if (!named && small_f8_misaligned(c, o, K)) {
+            t *= kSmallF8Misaligned;
+            try {
+                narrow = std::make_shared<skgemm_plan_s>(*c);
+            } catch (const std::bad_alloc&) {           // without it, only the calls it is for are refused
+            }
+        }
         if (!best || t < best_t || (t == best_t && tc < best_c)) {
             delete best;
             best = c;
@@ -865,6 +877,7 @@ static skgemm_status_t plan_variants(skgemm_plan_s* base, const skgemm_options_t
         }
     }
     if (!best) return last;
+    if (narrow && best->variant == 0) best->narrow = std::move(narrow);
     // An automatic single-GEMM plan that splits the small 16-bit tile's tiles
     // over more workgroups than CUs (two on some CUs) is replaced by a plan
     // of at most one workgroup per CU on the three-stage kernel where that
@@ -1144,13 +1157,14 @@ skgemm_status_t skgemm_grouped_plan(skgemm_plan_t* out, int32_t G, const int64_t
 
 skgemm_status_t skgemm_workspace_size(skgemm_plan_t plan, size_t* bytes) {
     if (!plan || !bytes) return SKGEMM_ERR_INVALID_ARG;
-    *bytes = plan->ws_total;
+    *bytes = plan->narrow ? std::max(plan->ws_total, plan->narrow->ws_total) : plan->ws_total;
     return SKGEMM_OK;
 }
 
 skgemm_status_t skgemm_trace_capacity(skgemm_plan_t plan, size_t* n_records) {
     if (!plan || !n_records) return SKGEMM_ERR_INVALID_ARG;
     *n_records = size_t(plan->grid) * size_t(plan->max_segs);
+    if (plan->narrow) *n_records = std::max(*n_records, size_t(plan->narrow->grid) * size_t(plan->narrow->max_segs));
     return SKGEMM_OK;
 }
 
@@ -1224,6 +1238,10 @@ static skgemm_status_t run_impl(skgemm_plan_t pl, const void* A, int64_t lda, co
     GroupEntry e;
     std::memset(&e, 0, sizeof(e));
     skgemm_status_t st = check_problem(pl, pl->M, pl->N, pl->K, A, lda, B, ldb, C, ldc, &e);
+    if (pl->narrow && (st == SKGEMM_ERR_UNSUPPORTED || (pl->ws_bytes && (!workspace || ws_bytes < pl->ws_bytes)))) {
+        pl = pl->narrow.get();
+        st = check_problem(pl, pl->M, pl->N, pl->K, A, lda, B, ldb, C, ldc, &e);
+    }
     if (st != SKGEMM_OK) return st;
     if (pl->M == 0 || pl->N == 0) return SKGEMM_OK;
     if (pl->ws_bytes) {
