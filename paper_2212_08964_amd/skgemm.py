@@ -542,7 +542,7 @@ def matmul(A, B, out=None, *, out_dtype=None, alpha=1.0, beta=0.0, scale_a=None,
         raise ValueError("matmul needs A (M x K) and B (K x N)")
     if A.dtype != B.dtype or A.dtype not in dts:
         raise ValueError(f"unsupported input dtypes {A.dtype}, {B.dtype}")
-    if not A.is_cuda or A.device != B.device or (out is not None and out.device != A.device):
+    if not A.is_cuda or A.device != B.device or not _in_reach(A.device, out):
         raise ValueError("operands must live on the same GPU")
     M, K = A.shape
     N = B.shape[1]
@@ -617,6 +617,12 @@ def _ws_ptr(nws, dev, stream):
     if ws is None or ws.numel() < nws:
         ws = workspace(nws, dev, stream)
     return ws.data_ptr()
+
+
+def _in_reach(dev, *tensors):
+    """Whether a kernel on dev can read and write these: its own memory, or pinned
+    host memory (whose calls are looked at every time, not remembered)."""
+    return all(t is None or t.device == dev or (t.device.type == "cpu" and t.is_pinned()) for t in tensors)
 
 
 def _scale_ptr(s, dev):
@@ -709,8 +715,8 @@ def grouped_matmul(As, Bs, Cs=None, *, out_dtype=None, alpha=1.0, beta=0.0, poli
             raise ValueError("beta != 0 needs Cs")
         Cs = [torch.empty((A.shape[0], B.shape[1]), dtype=out_dtype, device=dev) for A, B in zip(As, Bs)]
     # (an operand without elements is never read)
-    if any(t.numel() and (t.dtype != As[0].dtype or t.device != dev) for t in itertools.chain(As, Bs)) or \
-            any(C.numel() and (C.dtype != Cs[0].dtype or C.device != dev) for C in Cs):
+    if any(t.numel() and (t.dtype != As[0].dtype or not _in_reach(dev, t)) for t in itertools.chain(As, Bs)) or \
+            any(C.numel() and (C.dtype != Cs[0].dtype or not _in_reach(dev, C)) for C in Cs):
         raise ValueError("all operands (and all results) of a group must have one dtype and live on one GPU")
     pa, pb, pc = _pick(As, ROW_MAJOR), _pick(Bs, COL_MAJOR), _pick(Cs, ROW_MAJOR)
     if pa is None or pb is None or pc is None:
@@ -746,7 +752,7 @@ def grouped_matmul(As, Bs, Cs=None, *, out_dtype=None, alpha=1.0, beta=0.0, poli
                                 trace.data_ptr(), trace.numel() // 8, stream)
     if ws is not None and (_check_runs if check is None else check):
         check_workspace(ws, stream)
-    if fast and min(map(min, zip(Ms, Ns, Ks))) > 0:
+    if fast and min(map(min, zip(Ms, Ns, Ks))) > 0 and all(t.device == dev for t in itertools.chain(As, Bs)):
         # everything this call derived from the tensors' shapes, strides and
         # types, for the next call with the same signature
         if len(_gfast_cache) >= 256:
@@ -797,7 +803,7 @@ def batched_matmul(A, B, out=None, *, out_dtype=None, alpha=1.0, beta=0.0, polic
         raise ValueError("batched_matmul needs A (batch x M x K) and B (batch x K x N)")
     if A.dtype != B.dtype or A.dtype not in dts:
         raise ValueError(f"unsupported input dtypes {A.dtype}, {B.dtype}")
-    if not A.is_cuda or A.device != B.device or (out is not None and out.device != A.device):
+    if not A.is_cuda:
         raise ValueError("operands must live on the same GPU")
     batch, M, K = A.shape
     N = B.shape[2]
@@ -811,6 +817,8 @@ def batched_matmul(A, B, out=None, *, out_dtype=None, alpha=1.0, beta=0.0, polic
         B = B.contiguous()
         lb = _layout3(B, COL_MAJOR)
         fast = False
+    if not _in_reach(A.device, B, out):
+        raise ValueError("operands must live on the same GPU")
     if out is None:
         if beta != 0.0:
             raise ValueError("beta != 0 needs out")
@@ -839,7 +847,7 @@ def batched_matmul(A, B, out=None, *, out_dtype=None, alpha=1.0, beta=0.0, polic
                      trace_records=trace.numel() // 8 if trace is not None else 0)
     if ws is not None and _check_runs:
         check_workspace(ws, stream)
-    if fast and batch * M * N * K > 0:
+    if fast and batch * M * N * K > 0 and A.device == B.device:
         if len(_bfast_cache) >= 256:
             _bfast_cache.clear()
         _bfast_cache[fkey] = (plan, (batch, M, N), out.dtype, A.device, la[1], la[2], lb[1], lb[2], lc[1], lc[2], nws)
@@ -875,7 +883,7 @@ def conv2d(x, w, out=None, *, padding=(0, 0), stride=(1, 1), dilation=(1, 1), ou
         raise ValueError("conv2d needs x (N, H, W, C) and w (K, R, S, C)")
     if x.dtype != w.dtype or x.dtype not in (torch.bfloat16, torch.float16):
         raise ValueError(f"unsupported input dtypes {x.dtype}, {w.dtype}")
-    if not x.is_cuda or x.device != w.device or (out is not None and out.device != x.device):
+    if not x.is_cuda or not _in_reach(x.device, w, out):
         raise ValueError("operands must live on the same GPU")
     if not x.is_contiguous() or not w.is_contiguous():
         raise ValueError("conv2d needs contiguous channels-last x and w")
@@ -903,7 +911,7 @@ def conv2d(x, w, out=None, *, padding=(0, 0), stride=(1, 1), dilation=(1, 1), ou
         raise ValueError(f"out must be a contiguous ({n}, {P}, {Q}, {k}) {out_dtype} tensor")
     nws = plan.workspace_size()
     stream = torch.cuda.current_stream(x.device).cuda_stream
-    if fast and out.numel() and x.numel() and w.numel():
+    if fast and out.numel() and x.numel() and w.numel() and x.device == w.device:
         if len(_cfast_cache) >= 256:
             _cfast_cache.clear()
         _cfast_cache[fkey] = (plan, (n, P, Q, k), out_dtype, x.device, nws)

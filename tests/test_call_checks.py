@@ -292,3 +292,50 @@ def test_batched_and_conv_operand_elsewhere(launches, monkeypatch, kind, device)
         assert len(launches) == n
         if n == 0:
             call(a, b)
+
+
+@pytest.mark.parametrize("kind", ["matmul", "grouped", "batched", "conv"])
+def test_pinned_host_memory(grouped, monkeypatch, kind):
+    """A result in pinned host memory, and an operand where only the first one's
+    device counts, run as ever; the same signature in pageable memory does not
+    pass for them afterwards."""
+    seen = []
+
+    class Plan:
+        handle = object()
+
+        def __init__(self, *a, **k):
+            pass
+
+        def workspace_size(self):
+            return 0
+
+        def batched_run(self, *a, **k):
+            seen.append(a)
+
+        run = conv_run = grouped_run = batched_run
+        table = lambda self, args: bytes(128)
+
+    monkeypatch.setattr(skgemm, "get_plan", lambda *a: Plan())
+    for name in ("BatchedPlan", "ConvPlan", "GroupedPlan"):
+        monkeypatch.setattr(skgemm, name, Plan)
+    for name in ("_bplan_cache", "_bfast_cache", "_cplan_cache", "_cfast_cache"):
+        monkeypatch.setattr(skgemm, name, {})
+    monkeypatch.setattr(skgemm, "_layout3", lambda t, prefer: (skgemm.ROW_MAJOR, t.shape[2], t.stride(0)))
+    monkeypatch.setattr(Tensor, "is_contiguous", lambda self: True, raising=False)
+    shapes = {"matmul": ((8, 64), (64, 16), (8, 16)), "grouped": ((8, 64), (64, 16), (8, 16)),
+              "batched": ((2, 8, 64), (2, 64, 16), (2, 8, 16)), "conv": ((2, 4, 4, 64), (8, 1, 1, 64), (2, 4, 4, 8))}[kind]
+    call = {"matmul": skgemm.matmul, "batched": skgemm.batched_matmul, "conv": skgemm.conv2d,
+            "grouped": lambda a, b, c=None: skgemm.grouped_matmul([a], [b], c and [c])}[kind]
+    a, b = (Tensor(*s) for s in shapes[:2])
+    pinned = [Tensor(*s, device=HOST, pinned=True) for s in shapes]
+    call(a, b, pinned[2])
+    assert len(seen) == 1
+    if kind != "matmul":            # both operands of a product on one GPU, always
+        call(a, pinned[1])
+        call(a, pinned[1])
+        assert len(seen) == 3
+        with pytest.raises(ValueError, match="one GPU|same GPU"):
+            call(a, Tensor(*shapes[1], device=HOST))
+    with pytest.raises(ValueError, match="one GPU|same GPU"):
+        call(a, b, Tensor(*shapes[2], device=HOST))
