@@ -963,6 +963,8 @@ def quantize_e4m3(X, layout="row", out=None, scale=None):
         raise ValueError("out needs one contiguous dimension")
     if scale is None:
         scale = torch.empty(1, dtype=torch.float32, device=X.device)
+    if not _in_reach(X.device, out, scale):
+        raise ValueError("out and scale must live on X's GPU")
     # the maxima's buffer is this call's own: the allocator knows its stream, or the
     # capture it belongs to, and no other call's kernels write between this one's
     ws = torch.empty(_quantize_ws_bytes() // 4, dtype=torch.float32, device=X.device)

@@ -339,3 +339,21 @@ def test_pinned_host_memory(grouped, monkeypatch, kind):
             call(a, Tensor(*shapes[1], device=HOST))
     with pytest.raises(ValueError, match="one GPU|same GPU"):
         call(a, b, Tensor(*shapes[2], device=HOST))
+
+
+@pytest.mark.parametrize("device", [HOST, OTHER])
+def test_quantizer_results_elsewhere(launches, monkeypatch, device):
+    """Codes and scale are written through their addresses: memory that the kernel
+    cannot write is refused."""
+    monkeypatch.setattr(skgemm, "_qws_bytes", 4096)
+    monkeypatch.setattr(skgemm, "lib", lambda: types.SimpleNamespace(
+        skgemm_quantize_e4m3=lambda *a: launches.append(a) or skgemm.OK))
+    monkeypatch.setattr(torch, "empty", lambda *s, dtype=None, device=None: Tensor(
+        *(s[0] if isinstance(s[0], tuple) else s), dtype=dtype, device=device))
+    X = Tensor(16, 32)
+    for kw in (dict(out=Tensor(16, 32, dtype=torch.float8_e4m3fn, device=device)), dict(scale=scale(device=device))):
+        with pytest.raises(ValueError, match="X's GPU"):
+            skgemm.quantize_e4m3(X, **kw)
+    assert not launches
+    skgemm.quantize_e4m3(X, scale=scale(device=HOST, pinned=True))
+    assert len(launches) == 1
