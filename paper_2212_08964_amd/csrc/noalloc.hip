@@ -66,17 +66,25 @@ extern "C" skgemm_status_t skgemm_run_noalloc(skgemm_plan_t plan, const void* A,
     if (st != SKGEMM_OK) return st;
     // (what does not fit may still hold the plan's other tile: skgemm_run decides)
     const size_t need = std::min(size_t(info[28]), kScratchBytes);
-    if (need == 0) return skgemm_run(plan, A, lda, B, ldb, C, ldc, alpha, beta, scale_a, scale_b, nullptr, 0, stream);
-    void* ws = nullptr;
-    st = scratch_ptr(&ws);
-    if (st != SKGEMM_OK) return st;
-    const int64_t g_sk = need == kScratchBytes ? skg::kMaxFlagLines : info[13];
-    // The flags are left at zero by every run that completes its waits; an
-    // earlier run whose wait timed out (or that overlapped this one) may have
-    // left some raised, so the error word and this plan's flag lines are
-    // cleared first, on the same stream.
-    const int words = int((skg::kWsHeaderBytes + size_t(g_sk) * skg::kFlagStrideInts * 4) / 4);
-    clear_words<<<(words + 255) / 256, 256, 0, stream>>>(reinterpret_cast<int32_t*>(ws), words);
-    if (hipGetLastError() != hipSuccess) return SKGEMM_ERR_HIP;
-    return skgemm_run(plan, A, lda, B, ldb, C, ldc, alpha, beta, scale_a, scale_b, ws, need, stream);
+    int64_t lines = 0;
+    const size_t other = skg::other_tile_bytes(plan, &lines);
+    lines = std::max(lines, info[13]);
+    const auto run = [&](size_t bytes) {
+        void* ws = nullptr;
+        const skgemm_status_t rc = scratch_ptr(&ws);
+        if (rc != SKGEMM_OK) return rc;
+        // The flags are left at zero by every run that completes its waits; an
+        // earlier run whose wait timed out (or that overlapped this one) may have
+        // left some raised, so the error word and this plan's flag lines are
+        // cleared first, on the same stream.
+        const int words = int((skg::kWsHeaderBytes + size_t(lines) * skg::kFlagStrideInts * 4) / 4);
+        clear_words<<<(words + 255) / 256, 256, 0, stream>>>(reinterpret_cast<int32_t*>(ws), words);
+        if (hipGetLastError() != hipSuccess) return SKGEMM_ERR_HIP;
+        return skgemm_run(plan, A, lda, B, ldb, C, ldc, alpha, beta, scale_a, scale_b, ws, bytes, stream);
+    };
+    st = need ? run(need)
+              : skgemm_run(plan, A, lda, B, ldb, C, ldc, alpha, beta, scale_a, scale_b, nullptr, 0, stream);
+    // a leading dimension that only the plan's other tile can run, in more than this one's bytes
+    if (st == SKGEMM_ERR_WORKSPACE && need < other && other <= kScratchBytes) st = run(other);
+    return st;
 }

@@ -354,6 +354,13 @@ constexpr int kDefaultSpinLimit = 1 << 22;
 
 }  // namespace
 
+namespace skg {
+size_t other_tile_bytes(const skgemm_plan_s* plan, int64_t* lines) {
+    *lines = plan->narrow ? plan->narrow->g_sk : 0;
+    return plan->narrow ? plan->narrow->ws_bytes : 0;
+}
+}  // namespace skg
+
 extern "C" {
 
 void skgemm_default_options(skgemm_options_t* opt) {

@@ -4,6 +4,8 @@
 #include <stdint.h>
 #include <stddef.h>
 
+struct skgemm_plan_s;
+
 namespace skg {
 
 enum DType : int32_t { DT_F32 = 0, DT_F16 = 1, DT_BF16 = 2, DT_F8 = 3, DT_F64 = 4 };
@@ -154,5 +156,8 @@ int launch_quantize(int dtype, const void* x, int64_t rows, int64_t cols, int64_
                     int64_t ldq, bool q_col, float* scale, float* partial, void* stream);
 // FP32 scratch values the quantiser needs.
 int quant_workspace_floats();
+
+// Fix-up bytes and flag lines of the plan's other tile (0: it has none).
+size_t other_tile_bytes(const skgemm_plan_s* plan, int64_t* lines);
 
 }  // namespace skg

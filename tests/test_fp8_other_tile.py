@@ -43,6 +43,37 @@ def test_accepted_without_a_gpu():
     assert status(nws=small.workspace_size() - 1) == s.ERR_WORKSPACE
 
 
+@pytest.mark.skipif(torch.cuda.is_available(), reason="made-up addresses: only where nothing can be launched")
+@pytest.mark.parametrize("M,N,K", [(1922, 8252, 4018), (2786, 7310, 3898)])
+def test_library_array_without_a_gpu(M, N, K):
+    """The large tile's plan needs less than the small tile's: a leading dimension that
+    only the latter can run gets as far as looking for the library's array (ERR_HIP)."""
+    plan = s.Plan(M, N, K, lb=s.COL_MAJOR, ta=s.F8E4M3, tc=s.F32, num_cus=256, occupancy=2)
+    small = s.Plan(M, N, K, lb=s.COL_MAJOR, ta=s.F8E4M3, tc=s.F32, num_cus=256, occupancy=2, tile=(128, 128, 128))
+    assert plan.info()["tile"][:3] == (256, 256, 128)
+    assert plan.info()["fixup_ws_bytes"] < small.info()["fixup_ws_bytes"] <= 64 << 20
+
+    def status(lda):
+        return s.lib().skgemm_run_noalloc(plan.handle, 1 << 20, lda, 1 << 20, K, 1 << 20, N, 1.0, 0.0, None, None, None)
+
+    assert status(K) == s.ERR_HIP
+    assert status(8400003) == s.ERR_HIP
+    assert status(K - 1) == s.ERR_INVALID_ARG
+    assert status(17000000) == s.ERR_UNSUPPORTED
+
+
+@pytest.mark.gpu
+def test_library_array_of_the_other_tile():
+    """The same call on the GPU (rows 8400003 elements apart)."""
+    M, N, K, ld = 1922, 8252, 4018, 8400003
+    plan = s.Plan(M, N, K, lb=s.COL_MAJOR, ta=s.F8E4M3, tc=s.F32)
+    A, B = ints(M, K, 1, ld=ld), ints(N, K, 2).t()
+    C = torch.empty((M, N), device="cuda:0")
+    plan.run_noalloc(A.data_ptr(), ld, B.data_ptr(), K, C.data_ptr(), N, stream=torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(C, A.float() @ B.float())
+
+
 @pytest.mark.gpu
 def test_large_leading_dimension():
     M, N, K = 682, 4164, 7133
