@@ -25,7 +25,7 @@ int kernel_threads_f64(int v);
 enum Form {
     FORM_FULL = 1,       // with the group table, batch, trace and timestamp paths
     FORM_OUT32 = 2,      // for FP32 results
-    FORM_RAGGED = 4,     // for operands whose rows do not start on 16 bytes
+    FORM_RAGGED = 4,     // for operands whose rows do not start on 4 bytes
     FORMS = 8
 };
 
@@ -45,16 +45,21 @@ static const void* kernel_for(int dtype, bool akc, bool bkc, int v, int form) {
 
 static bool needs_full(const KArgs& a) { return a.G || a.batch > 1 || a.trace || a.times; }
 
-// The FP8 tile where either operand's rows start off 16 bytes.  The 16-bit one
-// where B's do (A's alone: 2176x2048x2047 37.8 us on the seam loop, 40.5 without)
-// and a workgroup runs more than 16 slabs of a tile: of 230 ragged launches the seam
-// loop's time goes to 0.97 (0.90-1.05) there, to 1.02 (0.96-1.11) with fewer.
-static bool ragged(int dtype, const KArgs& a) {
-    if (a.G) return false;              // the table's operands are not known here
-    if (dtype != DT_F8 && (a.t > a.sk_tiles ? a.ipt : a.sk_q) <= 16) return false;
+// Rows that do not start on 4 bytes, in launches whose workgroups run one tile or
+// share at most.  The 16-bit tile where B's do not (A's alone: 2176x2048x2047 37.8 us
+// on the seam loop, 40.5 without) and a workgroup runs more than 16 slabs (fewer:
+// mean 1.00): of 130 such launches the time goes from the seam loop's to 0.96 (0.91-1.03)
+// for shares and 0.99 (0.95-1.05) for whole tiles; of 48 with B's rows on 4 or 8 bytes
+// to 1.05 (0.99-1.15), of 11 whose workgroups go on to a second tile to 1.04.  The FP8 tile
+// where either operand's do not and more than one workgroup on a CU runs a share:
+// 0.99 (0.96-1.04) of 19; rows on 4 or 8 bytes 1.02, one workgroup on a CU 1.01, whole
+// tiles 1.02.
+static bool ragged(int dtype, const KArgs& a, int cus) {
+    if (a.G || a.t > a.grid) return false;              // (a table's operands are not known here)
+    if (dtype == DT_F8 ? a.dp_only || a.grid <= cus : (a.dp_only ? a.ipt : a.sk_q) <= 16) return false;
     const int eb = dtype == DT_F8 ? 1 : 2;
     const auto off = [&](const void* x, int64_t ld, int64_t stride) {
-        return ((reinterpret_cast<uintptr_t>(x) | uint64_t(ld * eb) | uint64_t(a.batch > 1 ? stride : 0)) & 15) != 0;
+        return ((reinterpret_cast<uintptr_t>(x) | uint64_t(ld * eb) | uint64_t(a.batch > 1 ? stride : 0)) & 3) != 0;
     };
     return off(a.B, a.ldb, a.stride_b) || (dtype == DT_F8 && off(a.A, a.lda, a.stride_a));
 }
@@ -90,9 +95,9 @@ int kernel_occupancy(int dtype, bool akc, bool bkc, int v) {
     return occ;
 }
 
-int launch_gemm(int dtype, bool akc, bool bkc, int v, const KArgs& args, int grid, void* stream) {
+int launch_gemm(int dtype, bool akc, bool bkc, int v, const KArgs& args, int grid, int cus, void* stream) {
     const int form = (needs_full(args) ? FORM_FULL : 0) | (args.out_dtype == DT_F32 ? FORM_OUT32 : 0) |
-                     (ragged(dtype, args) ? FORM_RAGGED : 0);
+                     (ragged(dtype, args, cus) ? FORM_RAGGED : 0);
     const void* f = kernel_for(dtype, akc, bkc, v, form);
     if (!f) return int(hipErrorInvalidDeviceFunction);
     KArgs copy = args;

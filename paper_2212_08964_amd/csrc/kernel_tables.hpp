@@ -63,14 +63,14 @@ const void* kernel_table(bool akc, bool bkc, int v) {
             case 13: return kc_only<DT, 13, FULL>(akc, bkc);   // 10 to 12 for FP32 results
             case 14: return kc_only<DT, 14, FULL>(akc, bkc);
             case 15: return any_layout<DT, 15, FULL>(akc, bkc);
-            case 16: return any_layout<DT, 16, FULL>(akc, bkc);  // 2 for rows off 16 bytes
+            case 16: return any_layout<DT, 16, FULL>(akc, bkc);  // 2 for rows off 4 bytes
             default: return nullptr;
         }
     } else if constexpr (DT == DT_F8) {
         switch (v) {
             case 0: return kc_only<DT, 0, FULL>(akc, bkc);
             case 1: return kc_only<DT, 1, FULL>(akc, bkc);
-            case 16: return kc_only<DT, 16, FULL>(akc, bkc);  // 1 for rows off 16 bytes
+            case 16: return kc_only<DT, 16, FULL>(akc, bkc);  // 1 for rows off 4 bytes
             default: return nullptr;
         }
     } else if constexpr (DT == DT_F64) {

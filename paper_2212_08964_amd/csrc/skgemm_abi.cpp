@@ -1296,7 +1296,7 @@ static skgemm_status_t run_impl(skgemm_plan_t pl, const void* A, int64_t lda, co
         a.stride_c = strides[2] * ec;
     }
     if (pl->grid == 0) return SKGEMM_OK;
-    const int rc = launch_gemm(pl->dtype, pl->akc, pl->bkc, pl->variant, a, pl->grid, stream);
+    const int rc = launch_gemm(pl->dtype, pl->akc, pl->bkc, pl->variant, a, pl->grid, int(pl->p) / std::max(1, int(pl->occ)), stream);
     return rc == int(hipSuccess) ? SKGEMM_OK : SKGEMM_ERR_HIP;
 }
 
@@ -1419,7 +1419,7 @@ static skgemm_status_t conv_impl(skgemm_plan_t pl, const void* x, const void* w,
     a.beta = beta;
     fill_schedule_args(pl, &a, workspace, trace, nullptr);
     if (pl->grid == 0) return SKGEMM_OK;
-    const int rc = launch_gemm(pl->dtype, pl->akc, pl->bkc, pl->variant, a, pl->grid, stream);
+    const int rc = launch_gemm(pl->dtype, pl->akc, pl->bkc, pl->variant, a, pl->grid, int(pl->p) / std::max(1, int(pl->occ)), stream);
     return rc == int(hipSuccess) ? SKGEMM_OK : SKGEMM_ERR_HIP;
 }
 
@@ -1477,7 +1477,7 @@ static skgemm_status_t grouped_impl(skgemm_plan_t pl, const void* table_dev, voi
     a.G = pl->G;
     fill_schedule_args(pl, &a, workspace, trace, nullptr);
     if (pl->grid == 0) return SKGEMM_OK;
-    const int rc = launch_gemm(pl->dtype, pl->akc, pl->bkc, pl->variant, a, pl->grid, stream);
+    const int rc = launch_gemm(pl->dtype, pl->akc, pl->bkc, pl->variant, a, pl->grid, int(pl->p) / std::max(1, int(pl->occ)), stream);
     return rc == int(hipSuccess) ? SKGEMM_OK : SKGEMM_ERR_HIP;
 }
 

@@ -123,8 +123,9 @@ struct KArgs {
 // 9: the same with the convolution gather, substituted for variant 4.
 // 10 and 11: the streaming tiles of 32 and 64 rows (both operands K-contiguous).
 // 12: the quarter-size 64x64 16-bit tile.  The launch takes 13 to 15, the same with
-// sums in blocks, for 10 to 12 with an FP32 result (variants of the kernels, not of plans), and 16 for the 16-bit variant 2 and the FP8
-// variant 1 where operands' rows do not start on 16 bytes.
+// sums in blocks, for 10 to 12 with an FP32 result (variants of the kernels, not of
+// plans), and 16 for the 16-bit variant 2 and the FP8 variant 1 where operands' rows
+// do not start on 4 bytes.
 constexpr int kVariants = 13;
 constexpr int kVariantDeep = 8;
 constexpr int kVariantDeepConv = 9;
@@ -142,8 +143,9 @@ constexpr bool is_conv_variant(int v) { return v == 3 || v == 4 || v == 7 || v =
 int launch_pack(const void* src, int64_t ld, int64_t lines, int64_t cols, void* dst, int64_t ldd, int eb,
                 void* stream);
 
-// Launch one Stream-K GEMM kernel.  Returns a hipError_t value.
-int launch_gemm(int dtype, bool a_kcontig, bool b_kcontig, int variant, const KArgs& args, int grid,
+// Launch one Stream-K GEMM kernel on the `cus` CUs it was planned for.  Returns a
+// hipError_t value.
+int launch_gemm(int dtype, bool a_kcontig, bool b_kcontig, int variant, const KArgs& args, int grid, int cus,
                 void* stream);
 // Workgroups of the kernel that fit on one CU at once (0 on failure).
 int kernel_occupancy(int dtype, bool a_kcontig, bool b_kcontig, int variant);

@@ -147,12 +147,12 @@ template <> struct Cfg<DT_BF16, 14> : Cfg<DT_F16, 11> {};
 template <> struct Cfg<DT_BF16, 15> : Cfg<DT_F16, 12> {};
 
 // The eight-wave 128x128 16-bit tile and the small FP8 tile for operands whose
-// rows do not start on 16 bytes.  Such rows' loads keep the memory pipeline busy
+// rows do not start on 4 bytes.  Such rows' loads keep the memory pipeline busy
 // two to three times as long, and with two workgroups on a CU the seam loop's
 // workgroups wait for them in step.  Bound by that pipeline, these kernels load a
 // slab in one burst and do not read ahead over the seam: 895x2709x5051 49.3 us on
 // the seam loop, 45.5 here; 3810x632x7775 75.5 and 71.3; FP8 558x3457x4994 31.0 and
-// 29.3.  With rows on 16 bytes the seam loop is 2-20 % faster.
+// 29.3.  With rows on 4 or 8 bytes the seam loop is 5 % faster, on 16 2-20 %.
 template <> struct Cfg<DT_F16, 16> : Cfg<DT_F16, 2> { static constexpr int WPE = 4; };
 template <> struct Cfg<DT_BF16, 16> : Cfg<DT_BF16, 2> { static constexpr int WPE = 4; };
 template <> struct Cfg<DT_F8, 16> : Cfg<DT_F8, 1> {};
@@ -392,7 +392,7 @@ struct Slab {
     // wholly inside the inner edge (no per-chunk checks).
     template <bool EDGE>
     __device__ __forceinline__ void issue(const i32x4& d, int k0, int K, int o0, int dout, uint32_t lds, int tid) const {
-        if constexpr (EDGE && UNIFORM) tid = opaque(tid);
+        if constexpr (EDGE && EB <= 2) tid = opaque(tid);
         const bool tail = EDGE && (KC ? (k0 + BK > K) : (o0 + R > dout));
         const int lim = KC ? (K - k0) : (dout - o0);
         lds += uint32_t(uni(tid >> 6)) * 1024;
@@ -405,6 +405,12 @@ struct Slab {
             }
             dma16(d, at, lds + j * NW * 1024);
         }
+    }
+
+    // The same for the next slab.
+    template <bool EDGE>
+    __device__ __forceinline__ void issue_next(int k0, int K, int o0, int dout, uint32_t lds, int tid) {
+        issue<EDGE>(next_desc(), k0, K, o0, dout, lds, tid);
     }
 
     // After the stage's loads have landed: clear the bytes past the edge of
@@ -421,7 +427,7 @@ struct Slab {
 #pragma unroll
         for (int j = 0; j < PER_WAVE; ++j) {
             const int kp = keep(j, tail, lim, tid);
-            const uint32_t at = UNIFORM ? chunk_off(j, tid) : voff[UNIFORM ? 0 : j];
+            const uint32_t at = EB <= 2 ? chunk_off(j, tid) : voff[UNIFORM ? 0 : j];
             // a chunk that starts past the operand's end has landed as zeros
             if (kp > 0 && kp < VE && at < nr) {
                 unsigned char* dst = lds + (w + j * NW) * 1024 + lane * 16;
@@ -534,7 +540,8 @@ struct ConvSlab {
     __device__ __forceinline__ uint32_t off() const { return voff[J]; }
 
     template <bool EDGE>
-    __device__ __forceinline__ void issue(const i32x4& d, int, int, int, int, uint32_t lds, int tid) const {
+    __device__ __forceinline__ void issue_next(int k0, int, int, int, uint32_t lds, int tid) {
+        const i32x4 d = prepare(k0, tid);
         lds += uint32_t(uni(tid >> 6)) * 1024;
 #pragma unroll
         for (int j = 0; j < PER_WAVE; ++j) dma16(d, voff[j], lds + j * NW * 1024);
@@ -1122,13 +1129,6 @@ struct Gemm {
                 ...);
     }
 
-    // Descriptor of slab `it`, the n-th of the pipeline.
-    template <class S>
-    static __device__ __forceinline__ i32x4 desc(S& s, int n, int it, int tid) {
-        if constexpr (kSeam) return s.prepare(it * BK, tid);
-        else return s.nth_desc(n);
-    }
-
     // Slab kbeg + J into stage J, checked from kedge on.
     template <int J>
     static __device__ __forceinline__ void prologue_one(const Prob& a, SA& sa, SB& sb, int kbeg,
@@ -1136,12 +1136,20 @@ struct Gemm {
                                                         int tid) {
         const int it = kbeg + J;
         if (it >= kend) return;
-        if (it < kedge) {
-            sa.template issue<false>(desc(sa, J, it, tid), it * BK, a.K, m0, a.M, lds_addr(st.template at<J>()), tid);
-            sb.template issue<false>(desc(sb, J, it, tid), it * BK, a.K, n0, a.N, lds_addr(st.template at<J>()) + SA::BYTES, tid);
+        if constexpr (kSeam) {
+            if (it < kedge) {
+                sa.template issue_next<false>(it * BK, a.K, m0, a.M, lds_addr(st.template at<J>()), tid);
+                sb.template issue_next<false>(it * BK, a.K, n0, a.N, lds_addr(st.template at<J>()) + SA::BYTES, tid);
+            } else {
+                sa.template issue_next<true>(it * BK, a.K, m0, a.M, lds_addr(st.template at<J>()), tid);
+                sb.template issue_next<true>(it * BK, a.K, n0, a.N, lds_addr(st.template at<J>()) + SA::BYTES, tid);
+            }
+        } else if (it < kedge) {
+            sa.template issue<false>(sa.nth_desc(J), it * BK, a.K, m0, a.M, lds_addr(st.template at<J>()), tid);
+            sb.template issue<false>(sb.nth_desc(J), it * BK, a.K, n0, a.N, lds_addr(st.template at<J>()) + SA::BYTES, tid);
         } else {
-            sa.template issue<true>(desc(sa, J, it, tid), it * BK, a.K, m0, a.M, lds_addr(st.template at<J>()), tid);
-            sb.template issue<true>(desc(sb, J, it, tid), it * BK, a.K, n0, a.N, lds_addr(st.template at<J>()) + SA::BYTES, tid);
+            sa.template issue<true>(sa.nth_desc(J), it * BK, a.K, m0, a.M, lds_addr(st.template at<J>()), tid);
+            sb.template issue<true>(sb.nth_desc(J), it * BK, a.K, n0, a.N, lds_addr(st.template at<J>()) + SA::BYTES, tid);
         }
     }
 
@@ -1279,7 +1287,7 @@ struct Gemm {
         (row(read_a<I>(s, As, wm, lane), acc.v[I]), ...);
     }
 
-    // ---- 16-bit rows that do not start on 16 bytes, two stages: each slab is
+    // ---- 16-bit rows that do not start on 4 bytes, two stages: each slab is
     // loaded in one burst, A first, as soon as the stage is free, and computed
     // without reads over the seam (see Cfg<., 16>).
     template <int... I>
@@ -1420,12 +1428,12 @@ struct Gemm {
     }
 
     static __device__ __forceinline__ void issue_a(const Prob& a, SA& sa, bool edge, int it, int m0, uint32_t lds, int tid) {
-        if (edge) sa.template issue<true>(sa.prepare(it * BK, tid), it * BK, a.K, m0, a.M, lds, tid);
-        else sa.template issue<false>(sa.prepare(it * BK, tid), it * BK, a.K, m0, a.M, lds, tid);
+        if (edge) sa.template issue_next<true>(it * BK, a.K, m0, a.M, lds, tid);
+        else sa.template issue_next<false>(it * BK, a.K, m0, a.M, lds, tid);
     }
     static __device__ __forceinline__ void issue_b(const Prob& a, SB& sb, bool edge, int it, int n0, uint32_t lds, int tid) {
-        if (edge) sb.template issue<true>(sb.prepare(it * BK, tid), it * BK, a.K, n0, a.N, lds, tid);
-        else sb.template issue<false>(sb.prepare(it * BK, tid), it * BK, a.K, n0, a.N, lds, tid);
+        if (edge) sb.template issue_next<true>(it * BK, a.K, n0, a.N, lds, tid);
+        else sb.template issue_next<false>(it * BK, a.K, n0, a.N, lds, tid);
     }
 
     // ---- streaming tiles: WK waves split the slab's k
