@@ -730,15 +730,14 @@ struct Gemm {
     // members picked by compile-time index: a pointer array indexed in a loop
     // would be moved to LDS per thread by the compiler.
     struct Stages {
-        unsigned char *s0, *s1, *s2, *s3, *s4;
+        unsigned char *s0, *s1, *s2, *s3;
         template <int J>
         __device__ __forceinline__ unsigned char* at() const {
-            static_assert(J >= 0 && J < NS, "stage index");
+            static_assert(J >= 0 && J < NS && NS <= 4, "stage index");
             if constexpr (J == 0) return s0;
             else if constexpr (J == 1) return s1;
             else if constexpr (J == 2) return s2;
-            else if constexpr (J == 3) return s3;
-            else return s4;
+            else return s3;
         }
     };
 
@@ -1063,8 +1062,6 @@ struct Gemm {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
     }
     static __device__ __forceinline__ void wait_slab(int newer) {
-        if constexpr (NS >= 5)
-            if (newer >= 3) return wait_vmem_le<LOADS * 3>();
         if constexpr (NS >= 4)
             if (newer >= 2) return wait_vmem_le<LOADS * 2>();
         if constexpr (NS >= 3)
@@ -1483,9 +1480,7 @@ struct Gemm {
             cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
         }
         sums.finish(acc);
-        step_barrier();
-        if constexpr (WK > 1) add_waves(lds, acc, wk, lane, std::make_integer_sequence<int, FM>{});
-        else step_barrier();
+        add_waves(lds, acc, wk, lane, std::make_integer_sequence<int, FM>{});
     }
 
     // Band I of the tile (its 32-row blocks) is added up by wave I mod WK, from
@@ -1542,30 +1537,30 @@ struct Gemm {
         if constexpr (kStream) {
             Sums sums(kend - kbeg);
             stream_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, sums, tid);
-            return;
-        }
-        wait_slab(min(NS - 2, kend - 1 - kbeg));
-        if (kbeg >= kedge) {
-            sa.fix_edge(0, kbeg * BK, a.K, m0, a.M, st.template at<0>(), tid);
-            sb.fix_edge(0, kbeg * BK, a.K, n0, a.N, st.template at<0>() + SA::BYTES, tid);
-        }
-        step_barrier();
-        if constexpr (kStream) {
-        } else if constexpr (kSeam) {
-            Sums sums(kend - kbeg);
-            if constexpr (kRagged) burst_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, tid);
-            else slab_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, sums, tid);
         } else {
-            Sums sums(kend - kbeg);
-            static_assert(!kBlocks32 || NS == 2, "two sets of accumulators");
-            for (int kk = kbeg;; kk += NS)
-                if (!steps(a, sa, sb, kk, kbeg, kend, kedge, m0, n0, st, acc, sums, tid,
-                           std::make_integer_sequence<int, NS>{}))
-                    break;
-            if constexpr (kBlocks32) {
-                // the last slab's sums (of slab kbeg in acc, kbeg + 1 in odd, ...)
-                add(sums.sum, (kend - kbeg) % 2 ? acc : sums.odd);
-                acc = sums.sum;
+            wait_slab(min(NS - 2, kend - 1 - kbeg));
+            if (kbeg >= kedge) {
+                sa.fix_edge(0, kbeg * BK, a.K, m0, a.M, st.template at<0>(), tid);
+                sb.fix_edge(0, kbeg * BK, a.K, n0, a.N, st.template at<0>() + SA::BYTES, tid);
+            }
+            step_barrier();
+            if constexpr (kSeam && kRagged) {
+                burst_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, tid);
+            } else if constexpr (kSeam) {
+                Sums sums(kend - kbeg);
+                slab_loop(a, sa, sb, kbeg, kend, kedge, m0, n0, st, acc, sums, tid);
+            } else {
+                Sums sums(kend - kbeg);
+                static_assert(!kBlocks32 || NS == 2, "two sets of accumulators");
+                for (int kk = kbeg;; kk += NS)
+                    if (!steps(a, sa, sb, kk, kbeg, kend, kedge, m0, n0, st, acc, sums, tid,
+                               std::make_integer_sequence<int, NS>{}))
+                        break;
+                if constexpr (kBlocks32) {
+                    // the last slab's sums (of slab kbeg in acc, kbeg + 1 in odd, ...)
+                    add(sums.sum, (kend - kbeg) % 2 ? acc : sums.odd);
+                    acc = sums.sum;
+                }
             }
         }
     }
@@ -2195,13 +2190,13 @@ skgemm_kernel(KArgs a) {
     if constexpr (G::kSeam) {
         // one block: the MAC loop of these types picks its stages by offset
         __shared__ __attribute__((aligned(1024))) unsigned char st[G::NS * S];
-        typename G::Stages sts{st, st + S, st + 2 * S, st + 3 * S, st + 4 * S};
+        typename G::Stages sts{st, st + S, G::NS > 2 ? st + 2 * S : nullptr, G::NS > 3 ? st + 3 * S : nullptr};
         G::template run<FULL>(a, sts);
     } else {
         __shared__ __attribute__((aligned(1024))) unsigned char st0[S];
         __shared__ __attribute__((aligned(1024))) unsigned char st1[S];
         static_assert(G::NS == 2, "two stages");
-        typename G::Stages sts{st0, st1, nullptr, nullptr, nullptr};
+        typename G::Stages sts{st0, st1, nullptr, nullptr};
         G::template run<FULL>(a, sts);
     }
 }
