@@ -44,21 +44,28 @@ def estimate_terms(info):
     a partial wave at the per-iteration time interpolated between c (one
     busy slot) and e (all p slots busy); Stream-K plans pay a workgroup's
     data-parallel tiles, a, the fix-up terms b and d, and their share of
-    iterations at the time for g_sk busy slots.  The estimate is the dot
+    iterations at the time for g_sk busy slots.  The 64x64 16-bit and FP32 tiles
+    interpolate by the workgroups on the busiest CU instead.  The estimate is the dot
     product of these coefficients with the constants."""
     t, ipt, p = info["t"], info["ipt"], info["p"]
     g, skt, grid = info["g_sk"], info["sk_tiles"], info["grid"]
     if t == 0:
         return None
+    occ = max(1, info["occupancy"])
+
+    def busy(n):
+        if (info["BM"], info["BN"]) == (64, 64):
+            return (min(occ, math.ceil(n / (p // occ))) - 1) / (occ - 1) if occ > 1 else 0.0
+        return min(1.0, n / p)
     if g == 0:
         full, rem = divmod(t, p)
-        f = min(1.0, rem / p)
+        f = busy(rem)
         part = 1.0 if rem else 0.0
         return [full + part, 0.0, part * ipt * (1.0 - f), 0.0, full * ipt + part * ipt * f]
     ipc = math.ceil(skt * ipt / g)
     peers = max(1, math.ceil(ipt / ipc))
     dp_per_wg = math.ceil((t - skt) / grid)
-    f = min(1.0, g / p)
+    f = busy(g)
     return [1.0 + dp_per_wg, 1.0 if peers > 1 else 0.0, (1.0 - f) * ipc, float(peers - 1),
             dp_per_wg * ipt + f * ipc]
 
@@ -80,6 +87,8 @@ def sweep_shapes(n, seed):
 
 
 SWEEP_TILES = [(256, 256, 64, 8), (128, 128, 64, 4), (128, 128, 64, 8), (64, 256, 64, 4), (256, 64, 64, 4)]
+# the quarter-size tile, and the streaming tiles, which are timed on as many of a shape's rows as they have
+SMALL_TILES = [(64, 64, 64, 4), (32, 32, 256, 4), (64, 32, 256, 4)]
 
 
 def fit_sweep(n=1000, seed=1, dtype="bf16", verbose=True):
@@ -102,13 +111,14 @@ def fit_sweep(n=1000, seed=1, dtype="bf16", verbose=True):
     e1 = torch.cuda.Event(enable_timing=True)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
-    rows = {tile: ([], [], []) for tile in SWEEP_TILES}
-    for n_done, (M, N, K) in enumerate(sweep_shapes(n, seed)):
-        A = torch.randn((M, K), generator=gen, device="cuda").to(tdt)
+    rows = {tile: ([], [], []) for tile in SWEEP_TILES + SMALL_TILES}
+    for n_done, (rows_of_shape, N, K) in enumerate(sweep_shapes(n, seed)):
+        A = torch.randn((rows_of_shape, K), generator=gen, device="cuda").to(tdt)
         Bk = torch.randn((K, N), generator=gen, device="cuda").to(tdt)
         Bn = None
-        C = torch.empty((M, N), device="cuda", dtype=tdt)
-        for tile in SWEEP_TILES:
+        C = torch.empty((rows_of_shape, N), device="cuda", dtype=tdt)
+        for tile in SWEEP_TILES + SMALL_TILES:
+            M = min(rows_of_shape, tile[0]) if tile[2] == 256 else rows_of_shape
             lb, B = sk.ROW_MAJOR, Bk
             try:
                 plan = sk.Plan(M, N, K, ta=cdt, tc=cdt, policy="auto", tile=tile)

@@ -2,9 +2,13 @@
 sides of each limit, measured on both tiles (times in us, small tile / the other).
 A plan without a GPU has one co-residency for every tile, so the limits that weigh
 tiles against each other are checked with the device's own."""
+import os
+import subprocess
+import sys
+
 import pytest
 
-from paper_2212_08964_amd import skgemm as s
+from paper_2212_08964_amd import calibrate, skgemm as s
 
 QUARTER16, QUARTER32 = (64, 64, 64), (64, 64, 32)
 
@@ -88,3 +92,32 @@ def test_streaming_waves(M, N, K, stream):
 def test_streaming_64_rows(K, stream):
     """33 to 64 rows: up to 32 slabs (49x5120x11840: 40.2 / 33.0)."""
     assert (info(49, 5120, K, 0, 1, occupancy=2)["tile"][:3] == (64, 32, 256)) == stream
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("ta,tile", [(s.BF16, QUARTER16), (s.F32, QUARTER32)])
+def test_quarter_integer_shapes_take_the_tile(ta, tile):
+    """The shapes whose automatic products, single and batched by three, are compared
+    bit by bit with the oracle as this tile's."""
+    for M, N, K in [(500, 300, 1000), (130, 131, 77)]:
+        assert on_device(M, N, K, 0, 1, ta=ta)["tile"][:3] == tile
+        assert s.BatchedPlan(3, M, N, K, 0, 1, 0, ta, s.F32).info()["tile"][:3] == tile
+
+
+@pytest.mark.parametrize("tile", calibrate.SMALL_TILES)
+@pytest.mark.parametrize("M,N,K", [(32, 4096, 4096), (30, 1000, 333), (500, 300, 1000), (1024, 1024, 1024), (64, 9000, 2500),
+                                   (700, 900, 8192)])
+def test_calibration_terms(tile, M, N, K):
+    """calibrate.estimate_terms and the plan's constants give the planner's own
+    estimate (which its log prints, or its HBM bound where that is larger)."""
+    code = ("from paper_2212_08964_amd import skgemm as s, calibrate as c\n"
+            f"p = s.Plan({M}, {N}, {K}, lb=s.COL_MAJOR, ta=s.BF16, num_cus=256, occupancy=3, tile={tile})\n"
+            "print(sum(x * y for x, y in zip(c.estimate_terms(p.info()), p.model_constants())))")
+    out = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, SKGEMM_LOG="1"), capture_output=True, text=True,
+                         cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), timeout=120)
+    assert out.returncode == 0, out.stderr
+    logged = float(out.stderr.split("est_us=")[1].split()[0])
+    i = info(M, N, K, 0, 1, tile=tile)
+    hbm = 2.0 * (M * K + N * K + M * N) / 6.0e6
+    partials = 2.0 * 4 * i["BM"] * i["BN"] * (i["g_sk"] - i["sk_tiles"]) / 6.0e6 if i["g_sk"] else 0.0
+    assert logged == pytest.approx(max(float(out.stdout), hbm + partials), abs=0.02)
