@@ -26,13 +26,15 @@ enum Form {
     FORM_FULL = 1,       // with the group table, batch, trace and timestamp paths
     FORM_OUT32 = 2,      // for FP32 results
     FORM_RAGGED = 4,     // for operands whose rows do not start on 4 bytes
-    FORMS = 8
+    FORM_SHORT = 8,      // for short products
+    FORMS = 16
 };
 
 static const void* kernel_for(int dtype, bool akc, bool bkc, int v, int form) {
     const bool half = dtype == DT_F16 || dtype == DT_BF16, full = form & FORM_FULL;
     if (half && (form & FORM_OUT32)) v = with_block_sums(v);
     if ((form & FORM_RAGGED) && ((half && v == 2) || (dtype == DT_F8 && v == 1))) v = kKernelRagged;
+    if (dtype == DT_F32 && v == 1 && (form & FORM_SHORT)) v = kKernelShort;
     switch (dtype) {
         case DT_F32: return full ? kernel_fn_f32_full(akc, bkc, v) : kernel_fn_f32(akc, bkc, v);
         case DT_F16: return full ? kernel_fn_f16_full(akc, bkc, v) : kernel_fn_f16(akc, bkc, v);
@@ -63,6 +65,9 @@ static bool ragged(int dtype, const KArgs& a, int cus) {
     };
     return off(a.B, a.ldb, a.stride_b) || (dtype == DT_F8 && off(a.A, a.lda, a.stride_a));
 }
+
+// Up to eight slabs of the FP32 quarter-size tile (a group's products any number).
+static bool short_product(int dtype, const KArgs& a) { return dtype == DT_F32 && (a.G || a.ipt <= 8); }
 
 bool kernel_exists(int dtype, bool akc, bool bkc, int v) {
     for (int form = 0; form < FORMS; ++form)
@@ -97,7 +102,7 @@ int kernel_occupancy(int dtype, bool akc, bool bkc, int v) {
 
 int launch_gemm(int dtype, bool akc, bool bkc, int v, const KArgs& args, int grid, int cus, void* stream) {
     const int form = (needs_full(args) ? FORM_FULL : 0) | (args.out_dtype == DT_F32 ? FORM_OUT32 : 0) |
-                     (ragged(dtype, args, cus) ? FORM_RAGGED : 0);
+                     (ragged(dtype, args, cus) ? FORM_RAGGED : 0) | (short_product(dtype, args) ? FORM_SHORT : 0);
     const void* f = kernel_for(dtype, akc, bkc, v, form);
     if (!f) return int(hipErrorInvalidDeviceFunction);
     KArgs copy = args;

@@ -84,6 +84,7 @@ const void* kernel_table(bool akc, bool bkc, int v) {
         switch (v) {
             case 0: return any_layout<DT, 0, FULL>(akc, bkc);
             case 1: return any_layout<DT, 1, FULL>(akc, bkc);
+            case kKernelShort: return any_layout<DT, kKernelShort, FULL>(akc, bkc);  // 1 for short products
             default: return nullptr;
         }
     }

@@ -125,7 +125,7 @@ struct KArgs {
 // 12: the quarter-size 64x64 16-bit tile.  The launch takes 13 to 15, the same with
 // sums in blocks, for 10 to 12 with an FP32 result (variants of the kernels, not of
 // plans), and 16 for the 16-bit variant 2 and the FP8 variant 1 where operands' rows
-// do not start on 4 bytes.
+// do not start on 4 bytes, and 17 for the FP32 variant 1 on a short product.
 constexpr int kVariants = 13;
 constexpr int kVariantDeep = 8;
 constexpr int kVariantDeepConv = 9;
@@ -133,6 +133,7 @@ constexpr int kVariantQuarter = 12;
 constexpr int kVariantStream32 = 10;
 constexpr int kVariantStream64 = 11;
 constexpr int kKernelRagged = 16;
+constexpr int kKernelShort = 17;
 constexpr int with_block_sums(int v) { return v >= kVariantStream32 && v <= kVariantQuarter ? v + 3 : v; }
 constexpr bool is_stream_variant(int v) { return v == kVariantStream32 || v == kVariantStream64; }
 constexpr bool is_quarter_variant(int dt, int v) { return v == kVariantQuarter || (dt == DT_F32 && v == 1); }

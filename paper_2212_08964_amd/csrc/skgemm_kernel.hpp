@@ -157,6 +157,9 @@ template <> struct Cfg<DT_F16, 16> : Cfg<DT_F16, 2> { static constexpr int WPE =
 template <> struct Cfg<DT_BF16, 16> : Cfg<DT_BF16, 2> { static constexpr int WPE = 4; };
 template <> struct Cfg<DT_F8, 16> : Cfg<DT_F8, 1> {};
 
+// The FP32 quarter-size tile for short products (see Gemm::kBlock).
+template <> struct Cfg<DT_F32, kKernelShort> : Cfg<DT_F32, 1> {};
+
 // Optional tile traits: WPE overrides the waves per SIMD the register budget
 // is sized for.
 template <class C, class = void> struct ConvOf { static constexpr bool value = false; };
@@ -789,12 +792,16 @@ struct Gemm {
     // n + N / n, least at n = sqrt(N), where no cut into shares is more exact.
     // Relative error against 64 bits, 128x128 tile's shares / one chain / blocks:
     // 640x1280x1827 BF16 with an FP32 result 1.1e-7 / 2.5e-7 / 1.0e-7, FP32
-    // 384x384x1024 1.9e-7 / 2.3e-7 / 1.2e-7.  The FP32 tile's launches take 2-6 %
-    // longer for it (504x376x136 9.0 us against 8.5), the others' do not.
-    static constexpr bool kBlocks32 = DT == DT_F32 && V == 1;
+    // 384x384x1024 1.9e-7 / 2.2e-7 / 1.5e-7.  The FP32 tile's launches take 0-3 %
+    // longer for it (384x384x1024 14.0 us against 13.7), the others' do not.
+    static constexpr bool kBlocks32 = DT == DT_F32 && (V == 1 || V == kKernelShort);
     static constexpr bool kBlocks16 = kHalf && V > kVariantQuarter && V < kKernelRagged;
-    // FP32: a block is a slab, 16 MFMAs.  The slabs take turns between two sets of
-    // accumulators, so that one is added up behind the other's MFMAs.
+    // FP32: a block is two slabs, 32 MFMAs.  The blocks take turns between two sets of
+    // accumulators, so that one is added up behind the other's MFMAs.  Products of up to
+    // eight slabs, where the 128x128 tile's shares are single slabs, have a kernel whose
+    // blocks are single slabs too (1219x146x128 1.11e-7, 1.47e-7 with blocks of two; for
+    // longer ones it is 1-5 % slower, 321x341x4415 26.8 us against 25.3).
+    static constexpr int kBlock = V == kKernelShort ? 1 : 2;
     struct Turns {
         Acc sum, odd;
 
@@ -1093,13 +1100,18 @@ struct Gemm {
             }
         }
         if constexpr (kBlocks32) {
-            Acc &mine = U ? sums.odd : acc, &last = U ? acc : sums.odd;
-            zero(mine);
-            compute(cur, cur + SA::BYTES, mine, wm, wn, lane, [&] {
-                __builtin_amdgcn_sched_barrier(0);
-                add(sums.sum, last);
-                __builtin_amdgcn_sched_barrier(0);
-            });
+            constexpr bool ODD = U / kBlock % 2;
+            Acc &mine = ODD ? sums.odd : acc, &last = ODD ? acc : sums.odd;
+            if constexpr (U % kBlock) {
+                compute(cur, cur + SA::BYTES, mine, wm, wn, lane, [] {});
+            } else {
+                zero(mine);
+                compute(cur, cur + SA::BYTES, mine, wm, wn, lane, [&] {
+                    __builtin_amdgcn_sched_barrier(0);
+                    add(sums.sum, last);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            }
         } else {
             compute(cur, cur + SA::BYTES, acc, wm, wn, lane, [] {});
         }
@@ -1121,7 +1133,7 @@ struct Gemm {
     static __device__ __forceinline__ bool steps(const Prob& a, SA& sa, SB& sb, int kk, int kbeg,
                                                  int kend, int kedge, int m0, int n0, const Stages& st, Acc& acc,
                                                  Sums& sums, int tid, std::integer_sequence<int, U...>) {
-        return (step<U>(a, sa, sb, kk + U, kbeg, kend, kedge, m0, n0, st.template at<U>(),
+        return (step<U>(a, sa, sb, kk + U, kbeg, kend, kedge, m0, n0, st.template at<U % NS>(),
                         st.template at<(U + NS - 1) % NS>(), st.template at<(U + 1) % NS>(), acc, sums, tid) &&
                 ...);
     }
@@ -1552,13 +1564,14 @@ struct Gemm {
             } else {
                 Sums sums(kend - kbeg);
                 static_assert(!kBlocks32 || NS == 2, "two sets of accumulators");
-                for (int kk = kbeg;; kk += NS)
+                constexpr int UNROLL = kBlocks32 ? 2 * kBlock : NS;
+                for (int kk = kbeg;; kk += UNROLL)
                     if (!steps(a, sa, sb, kk, kbeg, kend, kedge, m0, n0, st, acc, sums, tid,
-                               std::make_integer_sequence<int, NS>{}))
+                               std::make_integer_sequence<int, UNROLL>{}))
                         break;
                 if constexpr (kBlocks32) {
-                    // the last slab's sums (of slab kbeg in acc, kbeg + 1 in odd, ...)
-                    add(sums.sum, (kend - kbeg) % 2 ? acc : sums.odd);
+                    // the last block's sums (of the first block in acc, the second in odd, ...)
+                    add(sums.sum, (kend - kbeg - 1) / kBlock % 2 ? sums.odd : acc);
                     acc = sums.sum;
                 }
             }
