@@ -42,8 +42,8 @@ METRIC = "TFLOP/s & % MFMA peak, Stream-K vs data-parallel tiles, bf16 shape swe
 # HBM bytes per GEMM kernel launch of the sweep, from two rocprofv3 PMC runs (FETCH_SIZE, WRITE_SIZE,
 # each scaled by its reading for a plain 256 MiB copy); valid only for the kernel sources
 # they were taken on, identified by the hash below (see profiles/skgemm_bf16_sweep_hbm_traffic.md).
-TRAFFIC_BYTES_PER_LAUNCH = 60.93e6
-TRAFFIC_SOURCES_SHA256 = "5d9a6fb7e5a2408e"
+TRAFFIC_BYTES_PER_LAUNCH = 59.34e6
+TRAFFIC_SOURCES_SHA256 = "1ce42a84f75402f2"
 
 
 def kernel_sources_hash() -> str:
@@ -766,8 +766,8 @@ def main():
                                "bf16 out, row-major",
                    "n_shapes": n, "shape_seed": args.shape_seed, "policy": "auto (DP waves + Stream-K remainder)",
                    "baseline": "same kernel and tile, policy=dp (one workgroup per tile)",
-                   "tiles": "256x256x64, or 128x128x64 (4 or 8 waves) where the planner predicts it faster "
-                            "(same tile for both)",
+                   "tiles": "256x256x64, 128x128x64 (8 waves, two or three stages) or 64x64x64 where the planner "
+                            "predicts it faster (same tile for both)",
                    "relayout": {"auto": "planner's rule (misaligned operand rows copied to 128-byte lines "
                                         "when predicted faster; the copy is timed)",
                                 "never": "off"}[args.relayout],
