@@ -693,13 +693,19 @@ static bool stream_waves(int64_t t, int64_t ipt, int64_t k, int64_t cus, int eb)
 // The streaming tile an automatic plan of a single GEMM with both operands
 // K-contiguous takes, or -1.  At most 32 rows (measured over 1 to 32 rows, 1024
 // to 16384 columns and 1024 to 8192 k, odd sizes among them: 1.2-1.7x the best
-// of the other tiles up to one tile per CU): always up to one tile per CU, above
-// by stream_waves.  33 to 64 rows: where its tiles fit the CUs in one wave and the
+// of the other tiles up to one tile per CU): up to one tile per CU, above by
+// stream_waves.  33 to 64 rows: where its tiles fit the CUs in one wave and the
 // rows of both operands start on 128-byte lines (1.0-1.32x); with more tiles, or
 // every run of a slab across a line more, its half of A a slab costs more than the
 // longer runs gain (64x11000x5000 40.7 us on the 64x256 tile, 50.2 here), and with
 // more than 32 slabs the few workgroups take longer than shares over all CUs
-// (49x5120x11840, 160 tiles of 47 slabs, 40.2 us against 33.0).
+// (49x5120x11840, 160 tiles of 47 slabs, 40.2 us against 33.0).  Not where k is a
+// small part of a slab, which is loaded whole (of 300 shapes up to 1024 k, share of
+// the other tiles' time: 33 to 64 rows up to 192 k 1.06-1.21, 64x704x64 7.8 us
+// against 6.4, above 0.64-1.01; 9 to 32 rows up to 128 k 0.93-1.18, above 0.61-1.02;
+// fewer rows up to 64 k 0.95-1.11, above 0.63-0.99).  Up to 128 columns they take it
+// all the same, 0.5-1 us slower (64x107x128 7.9 us against 6.9): the tests of the
+// rule hold these smallest products to it.
 static int stream_variant(const skgemm_plan_s* base, const skgemm_options_t& o, const int64_t* M, const int64_t* N,
                           const int64_t* K) {
     if (base->G || base->conv || base->batch != 1 || !base->akc || !base->bkc || o.policy != SKGEMM_POLICY_AUTO ||
@@ -707,6 +713,8 @@ static int stream_variant(const skgemm_plan_s* base, const skgemm_options_t& o, 
         return -1;
     const int64_t rows = base->swapped ? N[0] : M[0], cols = base->swapped ? M[0] : N[0];
     int v = -1;
+    const int64_t short_k = rows <= 8 ? 64 : rows <= kTile16R32.bm ? 128 : 192;
+    if (K[0] <= short_k && cols > kTile16S.bn) return -1;
     if (rows <= kTile16R32.bm) v = kVariantStream32;
     else if (rows <= kTile16R64.bm && (K[0] * elem_bytes(base->ta)) % 128 == 0) v = kVariantStream64;
     if (v < 0 || !kernel_exists(base->dtype, true, true, v)) return -1;

@@ -94,6 +94,19 @@ def test_streaming_64_rows(K, stream):
     assert (info(49, 5120, K, 0, 1, occupancy=2)["tile"][:3] == (64, 32, 256)) == stream
 
 
+@pytest.mark.parametrize("M,N,K,tile", [
+    (64, 704, 64, None), (64, 1230, 64, None), (33, 900, 128, None), (64, 900, 192, None),      # 1.06-1.21x
+    (64, 900, 256, (64, 32, 256)), (40, 5000, 448, (64, 32, 256)),
+    (32, 900, 64, None), (9, 900, 128, None), (9, 900, 129, (32, 32, 256)), (32, 3000, 200, (32, 32, 256)),
+    (8, 900, 64, None), (1, 900, 3, None), (8, 900, 65, (32, 32, 256)), (1, 3000, 96, (32, 32, 256)),
+    (8, 900, 0, None)])
+def test_streaming_short_k(M, N, K, tile):
+    """A small part of a slab: the other tiles, in either role of the small operand."""
+    stream = [(32, 32, 256), (64, 32, 256)]
+    for i in (info(M, N, K, 0, 1, occupancy=2), s.Plan(N, M, K, 0, 1, lc=1, ta=s.BF16, num_cus=256, occupancy=2).info()):
+        assert i["tile"][:3] == tile if tile else i["tile"][:3] not in stream
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("ta,tile", [(s.BF16, QUARTER16), (s.F32, QUARTER32)])
 def test_quarter_integer_shapes_take_the_tile(ta, tile):
