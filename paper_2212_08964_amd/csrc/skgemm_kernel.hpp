@@ -272,7 +272,14 @@ __device__ __forceinline__ int swz(int row) {
 // inner edge of a row (k beyond K, or columns beyond M or N) are skipped by
 // the wide load (offset forced out of range: zero, no memory access) and,
 // where partly inside, reloaded element by element.
-template <int EB, int R, int BK, bool KC, int THREADS>
+//
+// ONE_COL: the edge checks of chunks a uniform distance apart (below) share one
+// column and the loop's offsets.  With every chunk's own computed anew, FP8 launches
+// of up to 4 slabs and k off 16 took 4 % longer (855x1379x231 12.5 us against 11.7),
+// ragged 16-bit ones 1-3 %.  Not in the full kernels and the convolutions, where the
+// loop's code comes out worse with it (32 x 128x256x2048 14.2 us, 13.95 without;
+// 28x28x128 3x3 17.3 and 17.1).
+template <int EB, int R, int BK, bool KC, int THREADS, bool ONE_COL = false>
 struct Slab {
     static constexpr int VE = 16 / EB;
     static constexpr int ROWB = KC ? BK * EB : R * EB;      // LDS row bytes
@@ -376,7 +383,7 @@ struct Slab {
 
     // Elements of the lane's chunk j inside the inner edge (VE when not at the edge).
     __device__ __forceinline__ int keep(int j, bool tail, int lim, int tid) const {
-        return tail ? min(max(lim - chunk_col(j, tid) * VE, 0), VE) : VE;
+        return tail ? min(max(lim - chunk_col(UNIFORM && ONE_COL ? 0 : j, tid) * VE, 0), VE) : VE;
     }
 
     // A chunk that reaches past the inner edge but whose 16 bytes all lie
@@ -430,7 +437,7 @@ struct Slab {
 #pragma unroll
         for (int j = 0; j < PER_WAVE; ++j) {
             const int kp = keep(j, tail, lim, tid);
-            const uint32_t at = EB <= 2 ? chunk_off(j, tid) : voff[UNIFORM ? 0 : j];
+            const uint32_t at = UNIFORM && ONE_COL ? voff[0] + uint32_t(j) * vstep : EB <= 2 ? chunk_off(j, tid) : voff[UNIFORM ? 0 : j];
             // a chunk that starts past the operand's end has landed as zeros
             if (kp > 0 && kp < VE && at < nr) {
                 unsigned char* dst = lds + (w + j * NW) * 1024 + lane * 16;
@@ -710,7 +717,7 @@ __device__ __forceinline__ double lds_f64(const unsigned char* lds, int outer, i
         return *reinterpret_cast<const double*>(lds + mn_addr<8, ROWB>(k, outer));
 }
 
-template <int DT, bool AKC, bool BKC, int V>
+template <int DT, bool AKC, bool BKC, int V, bool FULL>
 struct Gemm {
     using C_ = Cfg<DT, V>;
     static constexpr int EB = C_::EB, BM = C_::BM, BN = C_::BN, BK = C_::BK;
@@ -720,8 +727,8 @@ struct Gemm {
     static constexpr int FM = WTM / 32, FN = WTN / 32;    // 32x32 MFMA blocks per wave
     static constexpr bool CONV = ConvOf<C_>::value;
     static_assert(!CONV || (AKC && BKC && (DT == DT_BF16 || DT == DT_F16)), "convolution: 16-bit, filters K-contiguous");
-    using SA = typename Pick<CONV, ConvSlab<EB, BM, BK, THREADS>, Slab<EB, BM, BK, AKC, THREADS>>::type;
-    using SB = Slab<EB, BN, BK, BKC, THREADS>;
+    using SA = typename Pick<CONV, ConvSlab<EB, BM, BK, THREADS>, Slab<EB, BM, BK, AKC, THREADS, !FULL>>::type;
+    using SB = Slab<EB, BN, BK, BKC, THREADS, !FULL && !CONV>;
     static constexpr int STAGE = SA::BYTES + SB::BYTES;
     static constexpr int NS = C_::NS;
     static_assert(NS >= 2 && NS * STAGE <= 160 * 1024, "LDS budget");
@@ -2082,7 +2089,6 @@ struct Gemm {
     // walk and epilogue spill fewer scalars (the full form runs plain GEMMs
     // 2.3 % slower over the BF16 shape sweep).  Its problem fields pass
     // through opaque_prob each segment, as the full form's may change.
-    template <bool FULL>
     static __device__ __forceinline__ void run(const KArgs& a, const Stages& st) {
         const int tid = threadIdx.x;
         const int wg = logical_wg(blockIdx.x, a.grid, a.xcds);
@@ -2198,19 +2204,19 @@ struct Gemm {
 template <int DT, bool AKC, bool BKC, int V, bool FULL>
 __global__ void __launch_bounds__((kThreadsOf<DT, V>)) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<DT, V>)))
 skgemm_kernel(KArgs a) {
-    using G = Gemm<DT, AKC, BKC, V>;
+    using G = Gemm<DT, AKC, BKC, V, FULL>;
     constexpr int S = G::STAGE;
     if constexpr (G::kSeam) {
         // one block: the MAC loop of these types picks its stages by offset
         __shared__ __attribute__((aligned(1024))) unsigned char st[G::NS * S];
         typename G::Stages sts{st, st + S, G::NS > 2 ? st + 2 * S : nullptr, G::NS > 3 ? st + 3 * S : nullptr};
-        G::template run<FULL>(a, sts);
+        G::run(a, sts);
     } else {
         __shared__ __attribute__((aligned(1024))) unsigned char st0[S];
         __shared__ __attribute__((aligned(1024))) unsigned char st1[S];
         static_assert(G::NS == 2, "two stages");
         typename G::Stages sts{st0, st1, nullptr, nullptr};
-        G::template run<FULL>(a, sts);
+        G::run(a, sts);
     }
 }
 
