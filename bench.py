@@ -42,8 +42,8 @@ METRIC = "TFLOP/s & % MFMA peak, Stream-K vs data-parallel tiles, bf16 shape swe
 # HBM bytes per GEMM kernel launch of the sweep, from two rocprofv3 PMC runs (FETCH_SIZE, WRITE_SIZE,
 # each scaled by its reading for a plain 256 MiB copy); valid only for the kernel sources
 # they were taken on, identified by the hash below (see profiles/skgemm_bf16_sweep_hbm_traffic.md).
-TRAFFIC_BYTES_PER_LAUNCH = 59.34e6
-TRAFFIC_SOURCES_SHA256 = "1ce42a84f75402f2"
+TRAFFIC_BYTES_PER_LAUNCH = 59.22e6
+TRAFFIC_SOURCES_SHA256 = "c2188a0b2f4fe143"
 
 
 def kernel_sources_hash() -> str:

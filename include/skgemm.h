@@ -194,7 +194,13 @@ skgemm_status_t skgemm_plan(skgemm_plan_t* out, int64_t M, int64_t N, int64_t K,
  * 256-byte aligned and zero-filled once after allocation; the kernel leaves
  * its flags at zero again on success, so it can be reused without clearing,
  * also by other plans (the flag area is at the same place for every plan).
- * After SKGEMM_ERR_TIMEOUT it must be zero-filled again. */
+ * After SKGEMM_ERR_TIMEOUT it must be zero-filled again.  An automatic FP8 plan
+ * that takes the 256x256 tile for rows off 128 bytes holds the 128x128 tile's
+ * plan too, for calls that only that one can run (a leading dimension beyond the
+ * large tile's 32-bit offsets, a workspace that is too small for its partial
+ * tiles): the size, like the trace capacity, is the larger of the two, a traced
+ * run records the plan that ran, and skgemm_plan_info and skgemm_schedule describe
+ * the large tile's. */
 skgemm_status_t skgemm_workspace_size(skgemm_plan_t plan, size_t* bytes);
 
 /* Run a planned GEMM.  lda/ldb/ldc follow each operand's layout and must be
@@ -218,7 +224,8 @@ skgemm_status_t skgemm_run(skgemm_plan_t plan,
  * on until the process ends, so the caller passes no workspace.  Plans whose
  * fix-up workspace (plan_info field 28) exceeds 64 MiB are refused with
  * SKGEMM_ERR_WORKSPACE (e.g. more than 254 Stream-K workgroups with
- * 256x256 FP32 partial tiles); operands are multiplied as given (no
+ * 256x256 FP32 partial tiles), but for FP8 plans whose 128x128 tile fits (see
+ * skgemm_workspace_size); operands are multiplied as given (no
  * re-layout copy).  Allocates nothing: before the GEMM it
  * clears the error word and the plan's flag lines with a small kernel on
  * `stream` (capturable), then runs skgemm_run on the array.  All calls on

@@ -140,10 +140,14 @@ void model_for(int dt, int v, double* m) {
     // of several full waves), used for grids larger than the CU count and in
     // the comparison of tile variants.  FP8 shares the 16-bit constants of
     // the same tile size: same wave layout, twice the k per iteration at
-    // twice the MFMA rate.
+    // twice the MFMA rate.  Fitted on the MAC loops before the one over the slab seam
+    // (whose iterations take 0.8-0.9 of it): all but the quarter-size and streaming
+    // tiles', so that kQuarterGain and the limits of plan_variants and stream_variant,
+    // measured on both sides, decide between those and the others.
     if (dt == DT_F64 && v == 1) { m[0] = 7.98; m[1] = 1.22; m[2] = 2.04; m[3] = 1.13; m[4] = 3.84; return; }
     if (dt == DT_F64) { m[0] = 5.00; m[1] = 1.23; m[2] = 0.713; m[3] = 1.13; m[4] = 2.09; return; }
     // the quarter-size tiles: fits over 1-256 (fp32: 1-1024) workgroups, 1-8 shares a tile
+    // (calibrate.py's grid mode: 4.74, 1.11, 0.255, 0.546, 0.501; fp32 4.64, 1.21, 0.806, 0.539, 2.23)
     if (v == kVariantQuarter) { m[0] = 4.73; m[1] = 1.37; m[2] = 0.243; m[3] = 0.525; m[4] = 0.505; return; }
     if (dt == DT_F32 && v == 1) { m[0] = 4.55; m[1] = 1.37; m[2] = 0.807; m[3] = 0.585; m[4] = 2.580; return; }
     if (dt == DT_F32) { m[0] = 6.20; m[1] = 1.25; m[2] = 2.07; m[3] = 0.569; m[4] = 3.99; return; }
@@ -736,8 +740,9 @@ static bool small_f8_misaligned(const skgemm_plan_s* c, const skgemm_options_t& 
 
 // A quarter-size tile is taken where the model has it this much faster than the
 // others: it moves twice the operand bytes through L2, which the model's
-// constants, fitted on problems that stay in cache, do not see (1024x1024x4096,
-// modelled 5 % faster, measured 20.9 us against 20.0).
+// constants, fitted on problems that stay in cache, do not see, and the others'
+// constants are of a slower MAC loop (1024x1024x4096, modelled 5 % faster, measured
+// 20.9 us against 20.0).
 constexpr double kQuarterGain = 0.90;
 
 // The quarter-size tiles compete for automatic plans of one GEMM or batch; the
